@@ -851,20 +851,6 @@ __device__ __forceinline__ void fill_row(cplx<R>* row, double s, int nm) {
   }
 }
 
-// The same row in FP64, every entry multiplied by `scale` (a particle's charge
-// carried by its first row, so that the products of its rows include it),
-// entry k stored at row[k * stride].
-__device__ __forceinline__ void fill_row_scaled(cplx<double>* row, double s, int nm, double scale, int stride) {
-  const cplx<double> u = turn(s);
-  cplx<double> c = {1.0, 0.0};
-  row[nm * stride] = {scale, 0.0};
-  for (int m = 1; m <= nm; ++m) {
-    c = (m & 7) == 0 ? turn(double(m) * s) : cmul(c, u);
-    row[(nm + m) * stride] = {c.x * scale, c.y * scale};
-    row[(nm - m) * stride] = {c.x * scale, -c.y * scale};
-  }
-}
-
 // Coordinate r of (a, b) read as one array of 2 DIM values, with the index
 // resolved by selects (a runtime index into register arrays would place
 // them in scratch memory).
@@ -913,114 +899,217 @@ struct SegWalk {
   }
 };
 
-// Rebuild rho over the segments segs[i] = seg0 + i * NT (i < NS) of one
-// walker in FP64: rho = rho_fix + sum_p q_p exp(i G.r_p), particles taken
-// `tile` at a time through LDS phase tables (tabs: tile * DIM * (2nm+1)).
-// The first row of each particle's tables carries its charge, so a segment's
-// anchor already holds q_p exp(i G.r_p) and the walk along the segment (a
-// linear recurrence) keeps the factor.  Two particles per pass give two
-// independent chains; a pass reads all its table entries before its
-// arithmetic.  `pos` and `q` may point to global or LDS memory.  All NT
-// threads must call it.
-// rfix: the fixed ions' part to start from (NULL: S->rho_fix; a layered
-// system's second plane passes S->rho_fix1).
-template <int DIM, int NS, int NT = BLOCK>
-__device__ void rebuild_rho(cplx<double> (&acc)[NS][SEG], const uint32_t (&an)[NS], int seg0,
-                            const DevSys* __restrict__ S, const double* pos, const double* q, int n,
-                            cplx<double>* tabs, int tile = TILE_P, const double* rfix = nullptr) {
-  const int nseg = S->n_seg, nm = S->nm, tbl = 2 * nm + 1, pstride = DIM * tbl;
-  // tile layout: the tables of particles 2k and 2k + 1 interleaved entry by
-  // entry, so that a pass reads both particles' entries at one address and
-  // the next 16 bytes; entry (p, d, idx) at ((p / 2) pstride + d tbl + idx) 2 + p % 2
-  int off[NS][DIM];  // 2 x the anchor's entry in each row of one particle's tables
-#pragma unroll
-  for (int i = 0; i < NS; ++i) {
-    const int s = seg0 + i * NT;
-#pragma unroll
-    for (int d = 0; d < DIM; ++d) off[i][d] = 2 * (d * tbl + nm + unpack_n(an[i], d));
-#pragma unroll
-    for (int j = 0; j < SEG; ++j) {
-      if (s < nseg) {
-        const double* rf = (rfix ? rfix : S->rho_fix) + 2 * (size_t(j) * nseg + s);
-        acc[i][j] = {rf[0], rf[1]};
-      } else {
-        acc[i][j] = {0.0, 0.0};
-      }
-    }
+// ---------------------------------------------------------------------------
+// rho from the positions: rho(G) = rho_fix(G) + sum_p q_p exp(i G.r_p), FP64.
+//
+// The sum is a matrix product over the particles.  A column piece (n_1, n_2;
+// 4 Q consecutive n_3 centred on the half-integer c) has
+//   rho(c + x) = sum_p A_p exp(i x th_p),  A_p = q_p exp(i (n_1, n_2, c).th_p),
+//   x = +-(h + 1/2), h = 0 .. 2Q - 1,
+// and the four real sums of (Re A, Im A) times (cos, sin)((h + 1/2) th) give
+// the two entries c +- (h + 1/2): two multiply-adds per entry and particle,
+// where a walk along the column costs eight operations.  The sums run on the
+// FP64 matrix instruction with four 4 x 4 x 4 blocks (rows: 16 column pieces;
+// columns: cos and sin of two h; depth: four particles): its 16 cycles for 256
+// multiply-adds are what the vector unit takes (4.4 cycles for 64), without
+// padding to 16 columns, and its operands come one per lane, so that the
+// LDS reads (48 bytes per row and particle, 8 per block column) stay below
+// the arithmetic, which broadcasting the 2 Q phases of a particle to every
+// lane of a vector loop would not.  (16 x 16 x 4 blocks measured 84 cycles for
+// 1024 multiply-adds, a fifth slower.  Matrix and vector FP64 share the unit:
+// run together their times add.)
+// Bound by FP64 issue.  At N = 1024 (254 columns, 3960 entries) 1024 rebuilds by
+// the per-step calls take 0.84 ms with their accepts (1.66 ms by walking the
+// columns, eight operations per entry), 1024 energies 1.65 ms (2.2 ms).
+//
+// Lanes (operand A: piece l % 16, particle l / 16; operand B: column l % 4,
+// particle l / 16; result: column l % 4, piece 4 (l / 4 % 4) + l / 16).
+// Columns 2t and 2t + 1 of a block are cos and sin of one h, so a lane's
+// neighbour holds the other half of the pair: even lanes end with the entry
+// c + (h + 1/2), odd ones with c - (h + 1/2).
+//
+// Waves: NW per workgroup, gw of them (a power of two) share the pieces'
+// groups, NS groups per wave and pass (the longest with the shortest, the
+// groups being sorted by length), and NW / gw of them share the particles.
+// Their sums meet in `rc` (LDS, 1 KB per segment of the groups' longest pieces;
+// the tables' own may serve, such a pass being the only one), in a fixed order.
+// Each pass takes the particles `tile` at a time (a multiple of four) through LDS
+// phase tables at `tabs` (S->ph_stride bytes per particle).  `sink(idx, v,
+// pos)` receives each entry once: slot idx, the sum v without the fixed
+// ions, pos the entry's place in grp_w.  All threads must call it; the last
+// thing it does before the sinks is a barrier.
+typedef double f64x2 __attribute__((ext_vector_type(2)));
+
+__device__ __forceinline__ cplx<double> lds_entry(const char* p) {
+  const f64x2 v = *reinterpret_cast<const f64x2*>(p);
+  return {v.x, v.y};
+}
+
+// One run of at most 8 entries of a phase-table row: entry m is
+// scale exp(2 pi i (m + off) s), m = m0 .. min(m0 + 8, m1) - 1, powers from an
+// exactly reduced start (error below ~8 ulp).
+__device__ __forceinline__ void fill_run(char* row, double s, double off, int m0, int m1, double scale) {
+  const cplx<double> u = turn(s);
+  cplx<double> c = turn((double(m0) + off) * s);
+  c.x *= scale;
+  c.y *= scale;
+  const int e = min(m0 + 8, m1);
+  for (int m = m0; m < e; ++m) {
+    *reinterpret_cast<f64x2*>(row + 16 * m) = f64x2{c.x, c.y};
+    c = cmul(c, u);
   }
-  auto base = [&](int p) { return tabs + (p >> 1) * (2 * pstride) + (p & 1); };
-  auto entries = [&](int i, int p, cplx<double> (&e)[DIM]) {
-    const cplx<double>* t = base(p);
+}
+
+// The phase tables of particles p0 .. p0 + np - 1 (up to the next multiple of
+// four, empty ones, all zero): per particle the rows exp(i n th_d), n = 0 .. nmax[d], of
+// the leading dimensions (the first carries the charge) and
+// exp(i (h + 1/2) th_last), h = 0 .. ph_hn - 1.
+template <int DIM, int NT>
+__device__ __forceinline__ void fill_tables(const DevSys* __restrict__ S, const double* pos, const double* q, int p0,
+                                            int np, int turn_at, char* tabs) {
+  const int runs = S->ph_runs;  // of the longest row
+  const int stride = S->ph_stride;
+  const int np_pad = (np + 3) & ~3;
+  // another wave starts each time, as a tile seldom has work for all of them
+  for (int e = (threadIdx.x + 8 * turn_at) & (NT - 1); e < np_pad * DIM * runs; e += NT) {
+    const int row = e / runs, m0 = 8 * (e - row * runs);
+    const int pp = row / DIM, d = row - pp * DIM;
+    const bool last = d == DIM - 1;
+    const int off = last ? S->ph_ou : (d == 0 ? 0 : S->ph_o1);
+    const int m1 = last ? S->ph_hn : S->nmax[d] + 1;
+    if (m0 >= m1) continue;
+    char* t = tabs + pp * stride + off;
+    if (pp < np)
+      fill_run(t, pos[(p0 + pp) * DIM + d], last ? 0.5 : 0.0, m0, m1, d == 0 ? q[p0 + pp] : 1.0);
+    else
+      for (int m = m0; m < min(m0 + 8, m1); ++m) *reinterpret_cast<f64x2*>(t + 16 * m) = f64x2{0.0, 0.0};
+  }
+}
+
+__device__ __forceinline__ double flip_sign(double v, uint32_t mask) {
+  return __hiloint2double(__double2hiint(v) ^ int(mask), __double2loint(v));
+}
+
+template <int DIM, int NW, int NS, typename Sink>
+__device__ __forceinline__ void rho_build(const DevSys* __restrict__ S, const double* pos, const double* q, int n,
+                                          char* tabs, int tile, cplx<double>* rc, int gw, int g_lo, int g_hi,
+                                          Sink&& sink) {
+  static_assert(NS == 1 || NS == 2, "groups per wave and pass");
+  static_assert(GRP_QMAX == 6, "the block columns' reads are written out");
+  constexpr int NT = NW * 64;
+  const int lane = threadIdx.x & 63, wave = uniform_i(int(threadIdx.x) >> 6);
+  const int nks = NW / gw, wg = wave & (gw - 1), ks = wave / gw;
+  const int stride = S->ph_stride, ou = S->ph_ou;
+  char* const tabs1 = tabs + tile * stride;  // the tables of one tile are filled while the other's are read
+  for (int gp = g_lo; gp < g_hi; gp += NS * gw) {
+    int grp[NS], Q[NS], o0[NS], o1[NS], oc[NS];
+    uint32_t s1[NS], sc[NS];
+    double ax[NS][GRP_QMAX], ay[NS][GRP_QMAX];
 #pragma unroll
-    for (int d = 0; d < DIM; ++d) e[d] = ld_entry(t, off[i][d]);
-  };
-  auto product = [](const cplx<double> (&e)[DIM]) {
-    cplx<double> v = cmul(e[0], e[1]);
-    if (DIM == 3) v = cmul(v, e[DIM - 1]);
-    return v;
-  };
-  for (int p0 = 0; p0 < n; p0 += tile) {  // tile is even
-    const int np = min(tile, n - p0);
-    for (int e = threadIdx.x; e < np * DIM; e += NT) {  // row e: particle e / DIM, dimension e % DIM
-      const int pp = e / DIM, d = e - pp * DIM;
-      fill_row_scaled(base(pp) + 2 * d * tbl, pos[p0 * DIM + e], nm, d == 0 ? q[p0 + pp] : 1.0, 2);
+    for (int t = 0; t < NS; ++t) {
+      const int g = gp + (t == 0 ? wg : 2 * gw - 1 - wg);
+      grp[t] = g < g_hi ? g : g_lo;
+      Q[t] = uniform_i(g < g_hi ? S->grp_q[grp[t]] : 0);
+      const uint32_t pk = S->grp_col[grp[t] * 16 + (lane & 15)];
+      o0[t] = 16 * int(pk & 0xff);
+      o1[t] = S->ph_o1 + 16 * int((pk >> 8) & 0xff);
+      oc[t] = ou + 16 * int((pk >> 16) & 0xff);
+      s1[t] = (pk << 7) & 0x80000000u;  // bit 24: n_2 < 0
+      sc[t] = (pk << 6) & 0x80000000u;  // bit 25: the centre is negative
+#pragma unroll
+      for (int i = 0; i < GRP_QMAX; ++i) ax[t][i] = ay[t][i] = 0.0;
     }
+    fill_tables<DIM, NT>(S, pos, q, 0, min(tile, n), 0, tabs);
     __syncthreads();
-    // the step phase exp(2 pi i s_last) of a particle is one entry of its
-    // tables, read by every lane at the same address (an LDS broadcast)
-    auto step_phase = [&](int p) { return ld_entry(base(p), 2 * ((DIM - 1) * tbl + nm + 1)); };
-    const int npair = np >> 1;
-    // one pass: the pair (p, p + 1) with the entries a (particle p) and b
-    auto pass = [&](int i, int p, const cplx<double> (&a)[DIM], const cplx<double> (&b)[DIM]) {
-      if (seg0 + i * NT < nseg) {
-        SegWalk<double> w0(product(a), step_phase(p)), w1(product(b), step_phase(p + 1));
-#pragma unroll
-        for (int j = 0; j < SEG; ++j) {
-          acc[i][j].x = (acc[i][j].x + w0.cur.x) + w1.cur.x;
-          acc[i][j].y = (acc[i][j].y + w0.cur.y) + w1.cur.y;
-          if (j + 1 < SEG) {
-            w0.step(j);
-            w1.step(j);
+    for (int p0 = 0, b = 0; p0 < n; p0 += tile, b ^= 1) {
+      const int left = n - p0;
+      if (left > tile) fill_tables<DIM, NT>(S, pos, q, p0 + tile, min(tile, left - tile), p0 + tile, b ? tabs : tabs1);
+      const int np_pad = (min(tile, left) + 3) & ~3;
+      // uniform branches on the groups' lengths (Q[1] <= Q[0]: they are
+      // sorted); written as a switch, or as loops for every pair of lengths,
+      // the accumulators were copied from register to register around the
+      // branches (1024 rebuilds 1.02 ms)
+      if (Q[0] > 0) {
+        const char* base = (b ? tabs1 : tabs) + (4 * ks + (lane >> 4)) * stride;
+        for (int p = 4 * ks; p < np_pad; p += 4 * nks, base += 4 * nks * stride) {
+          const double* bu = reinterpret_cast<const double*>(base + ou + 8 * (lane & 3));
+          double bq[GRP_QMAX];
+          bq[0] = bu[0];
+          bq[1] = bu[4];
+          if (Q[0] > 2) {
+            bq[2] = bu[8];
+            bq[3] = bu[12];
           }
+          if (Q[0] > 4) {
+            bq[4] = bu[16];
+            bq[5] = bu[20];
+          }
+          cplx<double> a[NS];
+#pragma unroll
+          for (int t = 0; t < NS; ++t) {  // (an absent second group repeats the first piece's entries)
+            a[t] = lds_entry(base + o0[t]);
+            if (DIM == 3) {
+              cplx<double> e1 = lds_entry(base + o1[t]);
+              e1.y = flip_sign(e1.y, s1[t]);
+              a[t] = cmul(a[t], e1);
+            }
+            cplx<double> ec = lds_entry(base + oc[t]);
+            ec.y = flip_sign(ec.y, sc[t]);
+            a[t] = cmul(a[t], ec);
+          }
+#pragma unroll
+          for (int i = 0; i < GRP_QMAX; ++i)
+#pragma unroll
+            for (int t = 0; t < NS; ++t)
+              if (i < Q[t]) {
+                ax[t][i] = __builtin_amdgcn_mfma_f64_4x4x4f64(a[t].x, bq[i], ax[t][i], 0, 0, 0);
+                ay[t][i] = __builtin_amdgcn_mfma_f64_4x4x4f64(a[t].y, bq[i], ay[t][i], 0, 0, 0);
+              }
         }
       }
-    };
-    for (int pr = 0; pr < npair; ++pr)
-#pragma unroll
-      for (int i = 0; i < NS; ++i) {
-        cplx<double> a0[DIM], b0[DIM];
-        entries(i, 2 * pr, a0);
-        entries(i, 2 * pr + 1, b0);
-        pass(i, 2 * pr, a0, b0);
-      }
-    if (np & 1) {  // the tile's last particle, alone
-      const int p = np - 1;
-#pragma unroll
-      for (int i = 0; i < NS; ++i) {
-        cplx<double> a0[DIM];
-        entries(i, p, a0);
-        if (seg0 + i * NT < nseg) {
-          SegWalk<double> w0(product(a0), step_phase(p));
-#pragma unroll
-          for (int j = 0; j < SEG; ++j) {
-            acc[i][j].x += w0.cur.x;
-            acc[i][j].y += w0.cur.y;
-            if (j + 1 < SEG) w0.step(j);
-          }
-        }
-      }
+      __syncthreads();
     }
-    __syncthreads();
+    const bool odd = lane & 1;
+    for (int k2 = 0; k2 < nks; ++k2) {  // uniform: the particle shares in a fixed order
+      if (k2 == ks) {
+#pragma unroll
+        for (int t = 0; t < NS; ++t)
+#pragma unroll
+          for (int i = 0; i < GRP_QMAX; ++i)
+            if (i < Q[t]) {
+              const double x = ax[t][i], y = ay[t][i];
+              const double nx = dpp_all<0xB1>(x), ny = dpp_all<0xB1>(y);  // the neighbour's (quad_perm [1,0,3,2])
+              cplx<double> v = {odd ? nx + y : x - ny, odd ? ny - x : y + nx};
+              const int at = (S->grp_off[grp[t]] + i) * 64 + lane;
+              const int idx = S->grp_slot[at];
+              if (idx >= 0) {
+                const int at_rc = at - S->grp_off[g_lo] * 64;
+                if (k2 > 0) {
+                  v.x += rc[at_rc].x;
+                  v.y += rc[at_rc].y;
+                }
+                if (k2 + 1 < nks)
+                  rc[at_rc] = v;
+                else
+                  sink(idx, v, at);
+              }
+            }
+      }
+      if (nks > 1) __syncthreads();
+    }
   }
+}
+
+// Waves that share the groups of column pieces in rho_build: the fewest whose
+// NS groups each cover them in one pass, so that the others share the particles.
+__host__ __device__ __forceinline__ int rho_waves(int n_grp, int ns, int nw) {
+  int gw = 1;
+  while (gw < nw && ns * gw < n_grp) gw *= 2;
+  return gw;
 }
 
 // ---------------------------------------------------------------------------
 // launch helpers
-
-inline int spt_for(int n_seg) {
-  const int need = (n_seg + BLOCK - 1) / BLOCK;
-  return need <= 1 ? 1 : need <= 2 ? 2 : need <= 4 ? 4 : 8;
-}
 
 inline hipStream_t as_stream(void* s) { return static_cast<hipStream_t>(s); }
 
@@ -1044,6 +1133,15 @@ inline size_t up16(size_t x) { return (x + 15) & ~size_t(15); }
 
 constexpr size_t RUN_LDS_BUDGET = 160 * 1024;  // LDS per workgroup on gfx950
 constexpr int RUN_NO_FIT = -1;                 // the fused kernel's LDS does not fit: use the per-step kernels
+
+// Particles per phase-table tile of rho_build with its two tiles within `bytes` of LDS: a multiple
+// of four (a matrix instruction takes four particles), at least four, no more
+// than the largest walker needs.
+inline int rho_tile(const LaunchBatch& b, size_t bytes) {
+  const int most = std::min(TILE_MAX, (b.max_particles + 3) & ~3);
+  return std::max(4, std::min(most, int(bytes / (2 * size_t(b.max_ph))) & ~3));
+}
+inline size_t rho_lds(const LaunchBatch& b, int tile) { return 2 * size_t(tile) * size_t(b.max_ph); }
 
 // Workgroups of this kernel that fit on one CU by registers (4 SIMDs, 512
 // VGPRs per lane each); the fused kernel sizes its LDS so as not to lower it.

@@ -13,10 +13,12 @@
 // complex multiply per slot.  Slots are slot-planar (slot j of segment s at
 // j * n_seg + s) so that one wave instruction reads 64 consecutive entries.
 //
-// One workgroup of 256 threads (four wave64s) serves one walker in every
-// kernel; reductions are wave shuffles followed by a 4-entry LDS combine.
-// Nothing here is a dense contraction worth an MFMA: the phase work is
-// complex multiplies with K = 1 and the pair work is transcendental-bound.
+// One workgroup serves one walker in every kernel (256 threads in the energy
+// and per-step kernels); reductions are wave shuffles followed by an LDS
+// combine.  rho from the positions is a contraction over the particles and
+// runs on the FP64 matrix instructions (rho_build); a move's phases are
+// complex multiplies with depth 1 and the pair work is a reciprocal square
+// root and a polynomial, neither of which is one.
 //
 // This translation unit holds the energy, per-step delta/accept and rebuild
 // kernels, the fused kernel's dispatch, and the device memory helpers; the
@@ -30,8 +32,7 @@ namespace ewald {
 
 // ---------------------------------------------------------------------------
 // Energy: wrap positions, rho in FP64, reciprocal and Jastrow sums, real-space
-// pairs, constants.  SPT = segments per thread held in registers.  Both
-// precision forms compute the energy alike, in FP64: it adds ~N^2/4 pair terms
+// pairs, constants.  Both precision forms compute the energy alike, in FP64: it adds ~N^2/4 pair terms
 // of one sign (like charges), so any FP32 rounding bias of the pair function
 // would add up coherently, while in a move delta it cancels between the old
 // and new terms.  The pair loop works in the orthogonal-sublattice frame when
@@ -39,7 +40,7 @@ namespace ewald {
 // stored in the walker state.
 // UJ: the Jastrow value also takes the two-body polynomial term u over the
 // mobile pairs (Sec. 2.3, Eq. (8)).
-template <int DIM, int SPT, int PD, bool ORTHO, bool UJ>
+template <int DIM, int PD, bool ORTHO, bool UJ>
 __global__ __launch_bounds__(BLOCK, 4) void k_energy(const DevSys* __restrict__ systems,
                                                   const DevWalker* __restrict__ walkers,
                                                   const double* __restrict__ pos, char* __restrict__ state,
@@ -54,10 +55,10 @@ __global__ __launch_bounds__(BLOCK, 4) void k_energy(const DevSys* __restrict__ 
   WalkerHdr* hdr = reinterpret_cast<WalkerHdr*>(st);
   double* spos = reinterpret_cast<double*>(st + HDR_BYTES);
   double* rho = reinterpret_cast<double*>(st + HDR_BYTES + walker_pos_bytes(n, DIM));
-  // LDS: the rebuild's phase-table tiles first, then (in the same space) the
+  // LDS: the phase-table tiles first, then (in the same space) the
   // pair loop's positions and charges
   double* red = smem;                        // [4 * 4]
-  cplx<double>* tabs = reinterpret_cast<cplx<double>*>(smem + 16);
+  char* tabs = reinterpret_cast<char*>(smem + 16);
   double* lpos = smem + 16;                  // [DIM][lds_pos] in the pair loop's geometry (planar:
                                              // lanes reading consecutive particles hit consecutive banks)
   double* lq = lpos + lds_pos * DIM;         // [n]
@@ -81,63 +82,51 @@ __global__ __launch_bounds__(BLOCK, 4) void k_energy(const DevSys* __restrict__ 
   }
   __syncthreads();
 
-  // reciprocal space
-  uint32_t an[SPT];
-#pragma unroll
-  for (int i = 0; i < SPT; ++i) {
-    const int s = tid + i * BLOCK;
-    an[i] = s < nseg ? S->seg_n[s] : 0u;
-  }
+  // reciprocal space: every entry of rho goes to the state as it is formed, with
+  // its terms of the energy and the Jastrow value
   // a layered 2D system (two planes): rho of each plane, with the
   // cross-plane term 2 w_x Re(rho_0 conj(rho_1)); the second plane's rho
   // follows the first in the state
   const bool lay = DIM == 2 && S->n_layers > 1;
   const int n0 = lay ? S->n0 : n;
-  cplx<double> acc[SPT][SEG];
-  rebuild_rho<DIM, SPT>(acc, an, tid, S, spos, S->mobile_q, n0, tabs, tile);
+  const int gw = rho_waves(S->n_grp, 2, BLOCK / 64);
+  cplx<double>* rc = reinterpret_cast<cplx<double>*>(tabs);  // waves sharing the particles: one pass, after the tables' last use
+  double2* rho2 = reinterpret_cast<double2*>(rho);
+  const double2* gwt = reinterpret_cast<const double2*>(S->grp_w);
   double er = 0.0, ej = 0.0;
-#pragma unroll
-  for (int i = 0; i < SPT; ++i) {
-    const int s = tid + i * BLOCK;
-    if (s < nseg) {
-#pragma unroll
-      for (int j = 0; j < SEG; ++j) {
-        const size_t g = size_t(j) * nseg + s;
-        const double m2 = acc[i][j].x * acc[i][j].x + acc[i][j].y * acc[i][j].y;
-        er = fma(S->w[g], m2, er);
-        if (S->ja) ej = fma(S->ja[g], m2, ej);
-        rho[2 * g] = acc[i][j].x;
-        rho[2 * g + 1] = acc[i][j].y;
-      }
-    }
-  }
+  rho_build<DIM, BLOCK / 64, 2>(S, spos, S->mobile_q, n0, tabs, tile, rc, gw, 0, S->n_grp,
+                                [&](int idx, cplx<double> v, int at) {
+                                  if (nfix > 0) {
+                                    v.x += S->rho_fix[2 * idx];
+                                    v.y += S->rho_fix[2 * idx + 1];
+                                  }
+                                  const double2 w2 = gwt[at];
+                                  const double m2 = v.x * v.x + v.y * v.y;
+                                  er = fma(w2.x, m2, er);
+                                  ej = fma(w2.y, m2, ej);
+                                  rho2[idx] = {v.x, v.y};
+                                });
   if (lay) {
-    cplx<double> acc1[SPT][SEG];
-    rebuild_rho<DIM, SPT>(acc1, an, tid, S, spos + size_t(n0) * DIM, S->mobile_q + n0, n - n0, tabs, tile,
-                          S->rho_fix1);
-    double* rho1 = rho + 2 * size_t(SEG) * nseg;
-#pragma unroll
-    for (int i = 0; i < SPT; ++i) {
-      const int s = tid + i * BLOCK;
-      if (s < nseg) {
-#pragma unroll
-        for (int j = 0; j < SEG; ++j) {
-          const size_t g = size_t(j) * nseg + s;
-          const double m2 = acc1[i][j].x * acc1[i][j].x + acc1[i][j].y * acc1[i][j].y;
-          const double x = acc[i][j].x * acc1[i][j].x + acc[i][j].y * acc1[i][j].y;
-          er = fma(S->w[g], m2, er);
-          er = fma(2.0 * S->wx[g], x, er);
-          rho1[2 * g] = acc1[i][j].x;
-          rho1[2 * g + 1] = acc1[i][j].y;
-        }
-      }
-    }
+    __syncthreads();
+    double2* rho12 = rho2 + size_t(SEG) * nseg;
+    rho_build<DIM, BLOCK / 64, 2>(S, spos + size_t(n0) * DIM, S->mobile_q + n0, n - n0, tabs, tile, rc, gw, 0,
+                                  S->n_grp, [&](int idx, cplx<double> v, int at) {
+                                    if (nfix > 0) {
+                                      v.x += S->rho_fix1[2 * idx];
+                                      v.y += S->rho_fix1[2 * idx + 1];
+                                    }
+                                    const double2 v0 = rho2[idx];  // written by this thread
+                                    const double m2 = v.x * v.x + v.y * v.y;
+                                    er = fma(gwt[at].x, m2, er);
+                                    er = fma(2.0 * S->wx[idx], v0.x * v.x + v0.y * v.y, er);
+                                    rho12[idx] = {v.x, v.y};
+                                  });
   }
+  __syncthreads();  // the tables (and rc) are done with
 
   // real space: each unordered mobile pair once (pair i with i+1..i+(n-1)/2
   // cyclically, plus i+n/2 for i < n/2 when n is even), then every fixed ion
-  // positions in the pair loop's geometry replace the tiles (the rebuild
-  // ends with a barrier)
+  // positions in the pair loop's geometry replace the tables
   for (int i = tid; i < n; i += BLOCK) {
     double sv[DIM], x[DIM];
 #pragma unroll
@@ -637,50 +626,72 @@ __global__ __launch_bounds__(BLOCK) void k_accept(const DevSys* __restrict__ sys
 }
 
 // Rebuild rho in FP64 for walkers whose accepted-move counter reached K.
-// grid = (walkers, chunks); chunk c rebuilds segments [c*BLOCK, (c+1)*BLOCK).
+// grid = (walkers, chunks); chunk c rebuilds the groups of column pieces
+// [c REBUILD_GROUPS, (c + 1) REBUILD_GROUPS): one per wave, half of the waves
+// taking each half of the particles.  Few walkers are due at a time, so
+// a rebuild is spread over several workgroups of eight waves; more, smaller
+// chunks would repeat the phase tables and launch more workgroups that find
+// nothing to do.
+// Large batches take `per` walkers per workgroup in turn, as the launch of
+// workgroups that find nothing due costs more than two due walkers now and then
+// meeting in one (32,768 workgroups of 8 waves take 24 us).
 // The counter is reset by the next accept or run call, not here, so that
 // every chunk sees the same trigger.
+constexpr int REBUILD_NT = 512;
+constexpr int REBUILD_GROUPS = 4;
 template <int DIM>
-__global__ __launch_bounds__(BLOCK) void k_rebuild(const DevSys* __restrict__ systems,
-                                                   const DevWalker* __restrict__ walkers,
-                                                   char* __restrict__ state) {
+__global__ __launch_bounds__(REBUILD_NT) void k_rebuild(const DevSys* __restrict__ systems,
+                                                        const DevWalker* __restrict__ walkers,
+                                                        char* __restrict__ state, int tile, int n_walkers, int per) {
   extern __shared__ double smem[];
-  const DevWalker W = walkers[blockIdx.x];
-  const int chunk = blockIdx.y, tid = threadIdx.x;
+  const int g_lo = blockIdx.y * REBUILD_GROUPS;
+  // lane i looks at walker i of the workgroup's share (every wave alike)
+  const int w0 = blockIdx.x * per;
+  bool due_i = false;
+  if (int(threadIdx.x & 63) < min(per, n_walkers - w0)) {
+    const DevWalker Wi = walkers[w0 + (threadIdx.x & 63)];
+    const DevSys* Si = systems + Wi.sys;
+    due_i = Si->refresh_every > 0 && reinterpret_cast<const WalkerHdr*>(state + Wi.state_off)->counter >= Si->refresh_every &&
+            g_lo < Si->n_grp;
+  }
+  for (uint64_t due = __ballot(due_i); due != 0; due &= due - 1) {  // uniform
+  const DevWalker W = walkers[w0 + __builtin_ctzll(due)];
   const DevSys* __restrict__ S = systems + W.sys;
-  const int n = W.n_mobile, nseg = S->n_seg, K = S->refresh_every;
+  const int n = W.n_mobile, nseg = S->n_seg;
   char* st = state + W.state_off;
   WalkerHdr* hdr = reinterpret_cast<WalkerHdr*>(st);
-  if (K <= 0 || hdr->counter < K || chunk * BLOCK >= nseg) return;  // uniform per workgroup
   const double* spos = reinterpret_cast<const double*>(st + HDR_BYTES);
   double* rho = reinterpret_cast<double*>(st + HDR_BYTES + walker_pos_bytes(n, DIM));
-  cplx<double>* tabs = reinterpret_cast<cplx<double>*>(smem);
-  const int s = chunk * BLOCK + tid;
-  uint32_t an[1] = {s < nseg ? S->seg_n[s] : 0u};
+  const int g_hi = min(g_lo + REBUILD_GROUPS, S->n_grp);
+  const int gw = rho_waves(g_hi - g_lo, 1, REBUILD_NT / 64);
+  char* tabs = reinterpret_cast<char*>(smem);
+  double drift = 0.0;
   // a layered system: each plane from its own particles and ions
   const int n_planes = (DIM == 2 && S->n_layers > 1) ? 2 : 1;
   for (int l = 0; l < n_planes; ++l) {  // uniform
     const int p0 = l == 0 ? 0 : S->n0, p1 = n_planes == 1 ? n : (l == 0 ? S->n0 : n);
-    double* rl = rho + 2 * size_t(SEG) * nseg * l;
-    cplx<double> acc[1][SEG];
-    rebuild_rho<DIM, 1>(acc, an, chunk * BLOCK + tid, S, spos + size_t(p0) * DIM, S->mobile_q + p0, p1 - p0,
-                        tabs, TILE_P, l == 0 ? S->rho_fix : S->rho_fix1);
-    if (s < nseg) {
-      double drift = 0.0;
-#pragma unroll
-      for (int j = 0; j < SEG; ++j) {
-        const size_t g = size_t(j) * nseg + s;
-        drift = fmax(drift, fmax(fabs(acc[0][j].x - rl[2 * g]), fabs(acc[0][j].y - rl[2 * g + 1])));
-        rl[2 * g] = acc[0][j].x;
-        rl[2 * g + 1] = acc[0][j].y;
-      }
-      for (int off = 32; off > 0; off >>= 1) drift = fmax(drift, __shfl_xor(drift, off, 64));
-      if ((tid & 63) == 0)
-        atomicMax(reinterpret_cast<unsigned long long*>(&hdr->drift_max),
-                  static_cast<unsigned long long>(__double_as_longlong(drift)));
-    }
+    double2* rl = reinterpret_cast<double2*>(rho) + size_t(SEG) * nseg * l;
+    const double* rfix = S->n_fixed > 0 ? (l == 0 ? S->rho_fix : S->rho_fix1) : nullptr;
+    // the waves' shares meet in the tables' LDS (one pass, after their last use)
+    rho_build<DIM, REBUILD_NT / 64, 1>(S, spos + size_t(p0) * DIM, S->mobile_q + p0, p1 - p0, tabs, tile,
+                                       reinterpret_cast<cplx<double>*>(smem), gw, g_lo, g_hi,
+                                       [&](int idx, cplx<double> v, int) {
+                                         if (rfix) {
+                                           v.x += rfix[2 * idx];
+                                           v.y += rfix[2 * idx + 1];
+                                         }
+                                         const double2 old = rl[idx];
+                                         drift = fmax(drift, fmax(fabs(v.x - old.x), fabs(v.y - old.y)));
+                                         rl[idx] = {v.x, v.y};
+                                       });
+    __syncthreads();
   }
-  if (chunk == 0 && tid == 0) hdr->n_refresh += 1;
+  for (int off = 32; off > 0; off >>= 1) drift = fmax(drift, __shfl_xor(drift, off, 64));
+  if ((threadIdx.x & 63) == 0)
+    atomicMax(reinterpret_cast<unsigned long long*>(&hdr->drift_max),
+              static_cast<unsigned long long>(__double_as_longlong(drift)));
+  if (g_lo == 0 && threadIdx.x == 0) hdr->n_refresh += 1;
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -688,44 +699,32 @@ __global__ __launch_bounds__(BLOCK) void k_rebuild(const DevSys* __restrict__ sy
 
 namespace {
 
-template <int DIM, int SPT, int PD, bool ORTHO, bool UJ>
+template <int DIM, int PD, bool ORTHO, bool UJ>
 int energy_inst(const LaunchBatch& b, const double* pos, char* state, double* energy, double* jastrow,
                 void* stream) {
   const int lds_pos = even(b.max_particles);
-  const size_t rpart = size_t(DIM) * (2 * b.max_nm + 1) * sizeof(cplx<double>);
   const size_t head = 16 * 8, pairs = size_t(lds_pos) * (DIM + 1) * 8;
-  auto* kern = k_energy<DIM, SPT, PD, ORTHO, UJ>;
-  // rebuild tiles (sharing their LDS with the pair loop's positions) as
+  auto* kern = k_energy<DIM, PD, ORTHO, UJ>;
+  // phase-table tiles (sharing their LDS with the pair loop's positions) as
   // large as LDS allows without lowering the workgroups per CU that
-  // registers allow (four: the kernel is bounded to four waves per SIMD),
-  // at most 64
+  // registers allow (four: the kernel is bounded to four waves per SIMD)
   static const int per_cu = blocks_per_cu(kern, BLOCK);
   const size_t budget = RUN_LDS_BUDGET / size_t(per_cu);
-  int tile = budget > head ? int(std::min<size_t>((budget - head) / rpart, 64)) : 0;
-  tile = std::max(tile & ~1, TILE_P);  // even (the tiles interleave particle pairs)
-  const size_t lds = head + std::max(pairs, size_t(tile) * rpart);
+  const int tile = rho_tile(b, budget - head);
+  // waves that share the particles (few groups) add up their sums in the tables' place
+  const size_t share = rho_waves(b.min_grp, 2, BLOCK / 64) < BLOCK / 64 ? size_t(BLOCK / 64) * GRP_BYTES : 0;
+  const size_t lds = head + std::max({pairs, rho_lds(b, tile), share});
   if (int rc = allow_lds(kern, lds)) return rc;
   hipLaunchKernelGGL(kern, dim3(b.n_walkers), dim3(BLOCK), lds, as_stream(stream), b.d_sys, b.d_walk, pos, state,
                      energy, jastrow, lds_pos, tile);
   return last_launch();
 }
 
-template <int DIM, int PD, bool ORTHO, bool UJ>
-int energy_spt(const LaunchBatch& b, const double* pos, char* state, double* energy, double* jastrow,
-               void* stream) {
-  switch (spt_for(b.max_n_seg)) {
-    case 1: return energy_inst<DIM, 1, PD, ORTHO, UJ>(b, pos, state, energy, jastrow, stream);
-    case 2: return energy_inst<DIM, 2, PD, ORTHO, UJ>(b, pos, state, energy, jastrow, stream);
-    case 4: return energy_inst<DIM, 4, PD, ORTHO, UJ>(b, pos, state, energy, jastrow, stream);
-    default: return energy_inst<DIM, 8, PD, ORTHO, UJ>(b, pos, state, energy, jastrow, stream);
-  }
-}
-
 template <int DIM, int PD, bool ORTHO>
 int energy_pd(const LaunchBatch& b, const double* pos, char* state, double* energy, double* jastrow,
               void* stream) {
-  return b.has_u ? energy_spt<DIM, PD, ORTHO, true>(b, pos, state, energy, jastrow, stream)
-                 : energy_spt<DIM, PD, ORTHO, false>(b, pos, state, energy, jastrow, stream);
+  return b.has_u ? energy_inst<DIM, PD, ORTHO, true>(b, pos, state, energy, jastrow, stream)
+                 : energy_inst<DIM, PD, ORTHO, false>(b, pos, state, energy, jastrow, stream);
 }
 
 template <int DIM>
@@ -777,10 +776,14 @@ int delta_dim(const LaunchBatch& b, char* state, const int32_t* k, const double*
 
 template <int DIM>
 int rebuild_launch(const LaunchBatch& b, char* state, void* stream) {
-  const size_t lds_r = size_t(TILE_P) * DIM * (2 * b.max_nm + 1) * sizeof(cplx<double>);
-  const int chunks = (b.max_n_seg + BLOCK - 1) / BLOCK;
-  hipLaunchKernelGGL((k_rebuild<DIM>), dim3(b.n_walkers, chunks), dim3(BLOCK), lds_r, as_stream(stream), b.d_sys,
-                     b.d_walk, state);
+  const int tile = rho_tile(b, RUN_LDS_BUDGET / 2);
+  const int chunks = (b.max_grp + REBUILD_GROUPS - 1) / REBUILD_GROUPS;
+  const size_t lds = std::max(rho_lds(b, tile), size_t(REBUILD_GROUPS) * GRP_BYTES);
+  auto* kern = k_rebuild<DIM>;
+  if (int rc = allow_lds(kern, lds)) return rc;
+  const int per = std::max(1, std::min(16, b.n_walkers / 512));
+  hipLaunchKernelGGL(kern, dim3((b.n_walkers + per - 1) / per, chunks), dim3(REBUILD_NT), lds, as_stream(stream),
+                     b.d_sys, b.d_walk, state, tile, b.n_walkers, per);
   return last_launch();
 }
 

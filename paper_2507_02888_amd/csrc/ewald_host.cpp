@@ -338,6 +338,8 @@ struct ewald_sys {
   std::vector<uint32_t> seg_n;       // [n_seg]
   std::vector<int32_t> slot_n;       // slot-planar [n_slots][3]
   std::vector<double> w, ja;         // slot-planar [n_slots]
+  std::vector<int32_t> grp_q, grp_off, grp_slot;  // column pieces of the rho build (see DevSys)
+  std::vector<uint32_t> grp_col;
   std::vector<int32_t> shell;        // slot-planar, -1 for padding
   std::vector<double> shell_g2;      // |G|^2 of each shell
   std::vector<double> rho_fix;       // slot-planar [n_slots][2]
@@ -774,6 +776,70 @@ ewald_status ewald_setup(const ewald_sys_desc* desc, ewald_sys** out) try {
   }
   S->shell_g2 = shells;
 
+  // ---- column pieces for the rho build ----
+  {
+    struct Piece { int s0, q, n[3]; };
+    std::vector<Piece> pieces;
+    for (int a = 0; a < n_seg;) {
+      int b = a + 1;  // segments [a, b): one column
+      while (b < n_seg && segs[b].n[last] == segs[b - 1].n[last] + SEG) {
+        bool same = true;
+        for (int d = 0; d < last; ++d) same = same && segs[b].n[d] == segs[a].n[d];
+        if (!same) break;
+        ++b;
+      }
+      const int parts = (b - a + GRP_QMAX - 1) / GRP_QMAX;
+      for (int p = 0; p < parts; ++p) {
+        const int s0 = a + (b - a) * p / parts, s1 = a + (b - a) * (p + 1) / parts;
+        Piece pc{s0, s1 - s0, {segs[s0].n[0], segs[s0].n[1], segs[s0].n[2]}};
+        pieces.push_back(pc);
+      }
+      a = b;
+    }
+    std::stable_sort(pieces.begin(), pieces.end(), [](const Piece& x, const Piece& y) { return x.q > y.q; });
+    const int n_grp = int((pieces.size() + 15) / 16);
+    S->grp_q.assign(n_grp, 0);
+    S->grp_off.assign(n_grp, 0);
+    S->grp_col.assign(size_t(n_grp) * 16, 0u);
+    int hn = 0, off = 0;
+    for (int g = 0; g < n_grp; ++g) {
+      S->grp_q[g] = pieces[size_t(g) * 16].q;
+      S->grp_off[g] = off;
+      off += S->grp_q[g];
+      hn = std::max(hn, 2 * ((S->grp_q[g] + 1) & ~1));  // block columns are read in pairs
+    }
+    S->grp_slot.assign(size_t(off) * 64, -1);
+    for (size_t i = 0; i < pieces.size(); ++i) {
+      const Piece& p = pieces[i];
+      const int g = int(i / 16), col = int(i % 16), len = SEG * p.q;
+      const int c2 = 2 * p.n[last] + len - 1;  // twice the centre (odd)
+      const int hc = (std::abs(c2) - 1) / 2;
+      hn = std::max(hn, hc + 1);
+      const int n1 = dim == 3 ? p.n[1] : 0;
+      S->grp_col[i] = uint32_t(p.n[0]) | uint32_t(std::abs(n1)) << 8 | uint32_t(hc) << 16 |
+                      (n1 < 0 ? 1u << 24 : 0u) | (c2 < 0 ? 1u << 25 : 0u);
+      for (int q = 0; q < p.q; ++q)
+        for (int lane = 0; lane < 64; ++lane) {
+          const int j = lane & 3, row = 4 * ((lane >> 2) & 3) + (lane >> 4);
+          if (row != col) continue;
+          const int h = 2 * q + (j >> 1);
+          const int x = (j & 1) ? len / 2 - 1 - h : len / 2 + h;  // place in the piece
+          S->grp_slot[size_t(S->grp_off[g] + q) * 64 + lane] = (x % SEG) * n_seg + p.s0 + x / SEG;
+        }
+    }
+    DevSys& D = S->dev;
+    D.n_grp = n_grp;
+    D.n_ent = off;
+    D.ph_hn = hn;
+    D.ph_o1 = 16 * (nmax[0] + 1);
+    D.ph_ou = D.ph_o1 + (dim == 3 ? 16 * (nmax[1] + 1) : 0);
+    D.ph_stride = D.ph_ou + 16 * hn;
+    if ((D.ph_stride / 16) % 2 == 0) D.ph_stride += 16;  // consecutive particles start in different banks
+    int rows = std::max(hn, nmax[0] + 1);
+    if (dim == 3) rows = std::max(rows, nmax[1] + 1);
+    D.ph_runs = (rows + 7) / 8;
+  }
+
   // ---- charges, fixed ions ----
   S->mobile_q.assign(desc->mobile_q, desc->mobile_q + desc->n_mobile);
   S->fixed_q.assign(desc->fixed_q, desc->fixed_q + desc->n_fixed);
@@ -1093,6 +1159,18 @@ ewald_status upload_sys(ewald_sys* s, int device) {
     for (size_t g = 0; g < ns; ++g)
       if (s->shell[g] >= 0) wxt[size_t(s->shell[g])] = s->wx[g];
   }
+  // weights in the order in which the rho build delivers its entries
+  std::vector<double> gw(s->grp_slot.size() * 2, 0.0);
+  for (size_t i = 0; i < s->grp_slot.size(); ++i)
+    if (s->grp_slot[i] >= 0) {
+      gw[2 * i] = s->w[size_t(s->grp_slot[i])];
+      gw[2 * i + 1] = s->ja[size_t(s->grp_slot[i])];
+    }
+  const size_t o_gq = take(s->grp_q.size() * 4);
+  const size_t o_go = take(s->grp_off.size() * 4);
+  const size_t o_gc = take(s->grp_col.size() * 4);
+  const size_t o_gs = take(s->grp_slot.size() * 4);
+  const size_t o_gw = take(gw.size() * 8);
   const size_t o_wxt = take(std::max<size_t>(1, wxt.size()) * 8);
   const size_t o_wa = take(wa.size() * 8);
   const size_t o_jg = take(jg2.size() * 8);
@@ -1113,6 +1191,11 @@ ewald_status upload_sys(ewald_sys* s, int device) {
   std::memcpy(host.data() + o_wa, wa.data(), wa.size() * 8);
   std::memcpy(host.data() + o_jg, jg2.data(), jg2.size() * 8);
   std::memcpy(host.data() + o_sl, sl.data(), sl.size() * 2);
+  std::memcpy(host.data() + o_gq, s->grp_q.data(), s->grp_q.size() * 4);
+  std::memcpy(host.data() + o_go, s->grp_off.data(), s->grp_off.size() * 4);
+  std::memcpy(host.data() + o_gc, s->grp_col.data(), s->grp_col.size() * 4);
+  std::memcpy(host.data() + o_gs, s->grp_slot.data(), s->grp_slot.size() * 4);
+  std::memcpy(host.data() + o_gw, gw.data(), gw.size() * 8);
   void* d = nullptr;
   int rc = dev_alloc(&d, off);
   if (rc) return fail(EWALD_E_NOMEM, std::string("device allocation failed: ") + dev_error_string(rc));
@@ -1138,6 +1221,11 @@ ewald_status upload_sys(ewald_sys* s, int device) {
   D.wa_tab = reinterpret_cast<const double*>(base + o_wa);
   D.jg2_tab = reinterpret_cast<const double*>(base + o_jg);
   D.slot_shell = reinterpret_cast<const uint16_t*>(base + o_sl);
+  D.grp_q = reinterpret_cast<const int32_t*>(base + o_gq);
+  D.grp_off = reinterpret_cast<const int32_t*>(base + o_go);
+  D.grp_col = reinterpret_cast<const uint32_t*>(base + o_gc);
+  D.grp_slot = reinterpret_cast<const int32_t*>(base + o_gs);
+  D.grp_w = reinterpret_cast<const double*>(base + o_gw);
   D.n_wtab = n_wtab;
   D.wtab_lds = (sh16 && n_wtab <= WTAB_MAX) ? 1 : 0;
   s->dev_uploaded = D;
@@ -1225,6 +1313,9 @@ ewald_status ewald_batch_create(ewald_sys* const* sys, int n_sys, const int* wal
     L.layered |= sys[i]->dev.n_layers > 1 ? 1 : 0;
     L.max_n_seg = std::max(L.max_n_seg, sys[i]->n_seg);
     L.max_nm = std::max(L.max_nm, sys[i]->dev.nm);
+    L.max_grp = std::max(L.max_grp, sys[i]->dev.n_grp);
+    L.min_grp = i == 0 ? sys[i]->dev.n_grp : std::min(L.min_grp, sys[i]->dev.n_grp);
+    L.max_ph = std::max(L.max_ph, sys[i]->dev.ph_stride);
     L.max_particles = std::max(L.max_particles, sys[i]->n_mobile);
     L.max_fixed = std::max(L.max_fixed, sys[i]->n_fixed);
     L.refresh_every = std::max(L.refresh_every, L.mixed ? sys[i]->refresh_every : 0);

@@ -21,9 +21,10 @@ constexpr int HDR_BYTES = 256;    // per-walker state header
 // Byte offset, in the state buffer (inside the first walker's header), of the
 // fused kernel's work counter when its workgroups take walkers from a queue.
 constexpr int QUEUE_OFF = 192;
-constexpr int MAX_SPT = 8;        // segments per thread held in registers (MAX_SEGMENTS / BLOCK)
-constexpr int TILE_P = 8;         // particles per phase-table tile when rebuilding rho (tiles are even)
-static_assert(TILE_P % 2 == 0, "rebuild tiles hold whole particle pairs");
+constexpr int GRP_QMAX = 6;       // longest column piece of the rho build, in segments
+constexpr size_t GRP_BYTES = size_t(GRP_QMAX) * 64 * 16;  // one group's entries
+constexpr int TILE_MIN = 8;       // fewest particles per phase-table tile that the launchers aim for
+constexpr int TILE_MAX = 64;      // most
 constexpr int RUN_CHUNK = 64;     // proposals staged in LDS per chunk by the fused kernel
 constexpr int WTAB_MAX = 1024;    // largest shell table kept in LDS by the fused kernel
 constexpr int POLY_MAX = 32;      // largest degree of the pair-potential polynomial (FP64)
@@ -119,6 +120,22 @@ struct DevSys {
   const double* jg2_tab;     // [n_wtab] Jastrow coefficient times |G|^2 per shell (0 for padding)
   int n_wtab;                // n_shells + 1 (a zero entry for padding slots)
   int wtab_lds;              // 1 if n_wtab <= WTAB_MAX: the fused kernel reads wa_tab from LDS
+  // rho build (rho_build): column pieces of at most GRP_QMAX segments, sorted
+  // by length and taken 16 at a time (a group).  grp_q: segments of a group's
+  // longest piece; grp_off: their running sum; grp_col: [n_grp][16] packed
+  // (n_1, |n_2| << 8, h_c << 16, n_2 < 0 << 24, c < 0 << 25) with the centre
+  // |c| = h_c + 1/2; grp_slot: [sum of grp_q][64] slot of each lane's entry (-1:
+  // none); grp_w: the same places, (weight, Jastrow coefficient).
+  // Phase tables of one particle: ph_stride bytes, the rows of dimension 1
+  // (3D) and of the last dimension at ph_o1 and ph_ou, ph_hn entries in the
+  // last, ph_runs runs of 8 entries in the longest row.
+  int n_grp, n_ent;  // groups; sum of grp_q
+  int ph_hn, ph_o1, ph_ou, ph_stride, ph_runs;
+  const int32_t* grp_q;
+  const int32_t* grp_off;
+  const uint32_t* grp_col;
+  const int32_t* grp_slot;
+  const double* grp_w;
   const double* fixed_s;     // [n_fixed][dim] wrapped fractional ion positions
   const double* fixed_q;     // [n_fixed]
   const double* mobile_q;    // [n_mobile]
@@ -166,6 +183,8 @@ struct LaunchBatch {
   int layered;              // any layered 2D system (the fused kernels with a second plane serve the sweep)
   int max_n_seg;
   int max_nm;
+  int max_grp, min_grp;     // most and fewest groups of column pieces over systems (rho build)
+  int max_ph;               // largest phase-table bytes per particle
   int max_particles;        // max n_mobile over systems
   int max_fixed;
   int refresh_every;        // max over systems (0: no rebuild kernel needed)

@@ -34,11 +34,43 @@ struct RunLds {
   // byte offsets into dynamic LDS; positions start at 0
   uint32_t q, red, wtab, ctab, sn, so, xn, xo, c2q, part, k, acc, cnt;
   uint32_t wtab2, part2;  // Jastrow derivatives: a |G|^2 per shell, and the per-move partial sums
-  uint32_t rcopy;  // 0, or the LDS copy of the running rho during a rebuild
+  uint32_t rbytes;  // LDS bytes that the rebuild between chunks may use, from ctab on
   uint32_t next;   // queue mode: the next walker's index, broadcast to the workgroup
   int ch;     // moves per chunk
-  int rtile;  // particles per rebuild tile (the tiles reuse the chunk tables)
+  int rtile;  // particles per phase-table tile of the rebuild (the tiles reuse the chunk tables)
 };
+
+// The mixed form's rebuild of one plane's rho (in the walker state) between
+// chunks; returns this thread's largest |running - rebuilt|.  The move loop
+// keeps nothing in registers across it (it writes its rho back and loads its
+// state again), as the 48 accumulators per lane would otherwise compete with
+// that state for the whole kernel: inlined among live registers, 134 of them
+// were spilled at 1024 threads and the move loop alone ran 1.3 times longer
+// (three times at 512 threads and four waves per SIMD).  2048 walkers x 512
+// moves at N = 1024, K = 64 (four rebuilds each): 14.6 ms at 1024 threads, 13.8 ms
+// at 512 and four waves per SIMD, against 17.8 and 16.1 ms with a rebuild that
+// walks the columns.
+// rc_bytes: LDS from tabs on.
+template <int DIM, int NW>
+__device__ __forceinline__ double run_rebuild(const DevSys* __restrict__ S, const double* pos, const double* q, int n, char* tabs,
+                                             int tile, uint32_t rc_bytes, const double* rfix, double* rho) {
+  // waves may share the particles where LDS holds their sums (in the tables' place)
+  const int gs = rho_waves(S->n_grp, 2, NW);
+  const bool fits = S->n_ent * 1024u <= rc_bytes;
+  double drift = 0.0;
+  cplx<double>* out = reinterpret_cast<cplx<double>*>(rho);
+  rho_build<DIM, NW, 2>(S, pos, q, n, tabs, tile, reinterpret_cast<cplx<double>*>(tabs), fits ? gs : NW, 0, S->n_grp,
+                        [&](int idx, cplx<double> v, int) {
+                          if (rfix) {
+                            v.x += rfix[2 * idx];
+                            v.y += rfix[2 * idx + 1];
+                          }
+                          const cplx<double> old = out[idx];
+                          drift = fmax(drift, fmax(fabs(v.x - old.x), fabs(v.y - old.y)));
+                          out[idx] = v;
+                        });
+  return drift;
+}
 
 // At least two waves per SIMD for workgroups of up to 512 threads (the
 // register budget stays within 256 per lane; without the bound the compiler
@@ -108,7 +140,6 @@ __global__ __launch_bounds__(NT, NT >= 1024 ? 4 : WV) void k_run(const DevSys* _
   double* red = reinterpret_cast<double*>(lds + L.red);
   WT2* ltab = reinterpret_cast<WT2*>(lds + L.wtab);
   cplx<R>* ctab = reinterpret_cast<cplx<R>*>(lds + L.ctab);
-  cplx<double>* tabs = reinterpret_cast<cplx<double>*>(lds + L.ctab);  // rebuild tiles, between chunks
   double* st_sn = reinterpret_cast<double*>(lds + L.sn);
   double* st_so = reinterpret_cast<double*>(lds + L.so);
   double* st_xn = reinterpret_cast<double*>(lds + L.xn);  // sn, so in the real-space geometry (ORTHO)
@@ -136,18 +167,6 @@ __global__ __launch_bounds__(NT, NT >= 1024 ? 4 : WV) void k_run(const DevSys* _
   double drift = hdr->drift_max;
   if (K > 0 && counter >= K) counter = 0;
 
-  double ps[PPR][DIM], pq[PPR];
-  int psp[PPR];  // UJ: spin labels of the thread's own particles
-#pragma unroll
-  for (int c = 0; c < PPR; ++c) {
-    const int j = tid + c * NT;
-    double sj[DIM];
-#pragma unroll
-    for (int d = 0; d < DIM; ++d) sj[d] = j < n ? spos[j * DIM + d] : 0.0;
-    geo_pos<DIM, ORTHO>(sj, S, ps[c]);
-    pq[c] = j < n ? S->mobile_q[j] : 0.0;
-    psp[c] = (UJ && j < n) ? S->spin[j] : 0;
-  }
   // Workgroups of up to 512 threads (256 vector registers per lane) hold the
   // pair-polynomial coefficients in vector registers for the whole sweep
   // (loaded with a lane-varying index, so they are not taken for scalars);
@@ -170,20 +189,11 @@ __global__ __launch_bounds__(NT, NT >= 1024 ? 4 : WV) void k_run(const DevSys* _
   FrameK fk{};  // with 1024 threads the constants are read where they are used
   if (CV) fk = frame_k_vector(S);
   uint32_t an[SPT];
-  cplx<double> rv[SPT][SEG];
-  cplx<double> rv2[LAY ? SPT : 1][SEG];  // LAY: the second plane
   uint32_t shp[SPT][SEG / 2];  // two 16-bit shell-table byte offsets per register
 #pragma unroll
   for (int i = 0; i < SPT; ++i) {
     const int s = tid + i * NT;
     an[i] = s < nseg ? S->seg_n[s] : 0u;
-#pragma unroll
-    for (int j = 0; j < SEG; ++j) {
-      const size_t g = size_t(j) * nseg + s;
-      rv[i][j] = s < nseg ? cplx<double>{rho[2 * g], rho[2 * g + 1]} : cplx<double>{0.0, 0.0};
-      if constexpr (LAY)
-        rv2[i][j] = (lay && s < nseg) ? cplx<double>{rho1[2 * g], rho1[2 * g + 1]} : cplx<double>{0.0, 0.0};
-    }
 #pragma unroll
     for (int j = 0; j < SEG; j += 2) {
       const size_t g = size_t(j) * nseg + s;
@@ -194,7 +204,35 @@ __global__ __launch_bounds__(NT, NT >= 1024 ? 4 : WV) void k_run(const DevSys* _
   }
   __syncthreads();
 
-  for (int m0 = 0; m0 < n_steps;) {
+  // from one rebuild (mixed form) to the next, or the whole sequence
+  for (int m0 = 0;;) {
+  double ps[PPR][DIM], pq[PPR];
+  int psp[PPR];  // UJ: spin labels of the thread's own particles
+#pragma unroll
+  for (int c = 0; c < PPR; ++c) {
+    const int j = tid + c * NT;
+    double sj[DIM];
+#pragma unroll
+    for (int d = 0; d < DIM; ++d) sj[d] = j < n ? lpos[j * DIM + d] : 0.0;
+    geo_pos<DIM, ORTHO>(sj, S, ps[c]);
+    pq[c] = j < n ? lq[j] : 0.0;
+    psp[c] = (UJ && j < n) ? S->spin[j] : 0;
+  }
+  cplx<double> rv[SPT][SEG];
+  cplx<double> rv2[LAY ? SPT : 1][SEG];  // LAY: the second plane
+#pragma unroll
+  for (int i = 0; i < SPT; ++i) {
+    const int s = tid + i * NT;
+#pragma unroll
+    for (int j = 0; j < SEG; ++j) {
+      const size_t g = size_t(j) * nseg + s;
+      rv[i][j] = s < nseg ? cplx<double>{rho[2 * g], rho[2 * g + 1]} : cplx<double>{0.0, 0.0};
+      if constexpr (LAY)
+        rv2[i][j] = (lay && s < nseg) ? cplx<double>{rho1[2 * g], rho1[2 * g + 1]} : cplx<double>{0.0, 0.0};
+    }
+  }
+
+  for (bool due = false; m0 < n_steps && !due;) {
     // ---- stage the chunk: proposals, old positions, accept counts ----
     const int cnt = min(CH, n_steps - m0);
     if (tid < cnt) {
@@ -471,84 +509,7 @@ __global__ __launch_bounds__(NT, NT >= 1024 ? 4 : WV) void k_run(const DevSys* _
         jlap[idx] = kq < 0 ? NAN : -2.0 * qk * sv[DIM] + 2.0 * qk * qk * S->jlap_c + (UJ ? sv[NDV - 1] : 0.0);
       }
     }
-    if (MIXED && K > 0 && counter >= K) {  // uniform: rebuild rho in FP64 between chunks
-      __syncthreads();  // the chunk's outputs have been read from the staging area
-      // keep the running rho for the drift check: in LDS when the layout has
-      // room for it, else in the walker state
-      cplx<double>* rc = reinterpret_cast<cplx<double>*>(lds + L.rcopy);
-#pragma unroll
-      for (int i = 0; i < SPT; ++i) {
-        const int s = tid + i * NT;
-        if (s < nseg)
-#pragma unroll
-          for (int j = 0; j < SEG; ++j) {
-            if (L.rcopy) {
-              rc[(i * NT + tid) * SEG + j] = rv[i][j];
-            } else {
-              const size_t g = size_t(j) * nseg + s;
-              rho[2 * g] = rv[i][j].x;
-              rho[2 * g + 1] = rv[i][j].y;
-            }
-          }
-      }
-      if constexpr (LAY) {
-        // a layered walker: the second plane's running rho kept in its state
-        // block, each plane rebuilt from its own particles and ions
-        if (lay) {
-#pragma unroll
-          for (int i = 0; i < SPT; ++i) {
-            const int s = tid + i * NT;
-            if (s < nseg)
-#pragma unroll
-              for (int j = 0; j < SEG; ++j) {
-                const size_t g = size_t(j) * nseg + s;
-                rho1[2 * g] = rv2[i][j].x;
-                rho1[2 * g + 1] = rv2[i][j].y;
-              }
-          }
-          rebuild_rho<DIM, SPT, NT>(rv2, an, tid, S, lpos + size_t(n0) * DIM, lq + n0, n - n0, tabs, L.rtile,
-                                    S->rho_fix1);
-        }
-      }
-      rebuild_rho<DIM, SPT, NT>(rv, an, tid, S, lpos, lq, n0, tabs, L.rtile);
-      double dm = 0.0;
-      if constexpr (LAY) {
-        if (lay) {
-#pragma unroll
-          for (int i = 0; i < SPT; ++i) {
-            const int s = tid + i * NT;
-            if (s < nseg)
-#pragma unroll
-              for (int j = 0; j < SEG; ++j) {
-                const size_t g = size_t(j) * nseg + s;
-                dm = fmax(dm, fmax(fabs(rv2[i][j].x - rho1[2 * g]), fabs(rv2[i][j].y - rho1[2 * g + 1])));
-              }
-          }
-        }
-      }
-#pragma unroll
-      for (int i = 0; i < SPT; ++i) {
-        const int s = tid + i * NT;
-        if (s < nseg)
-#pragma unroll
-          for (int j = 0; j < SEG; ++j) {
-            cplx<double> old;
-            if (L.rcopy) {
-              old = rc[(i * NT + tid) * SEG + j];
-            } else {
-              const size_t g = size_t(j) * nseg + s;
-              old = {rho[2 * g], rho[2 * g + 1]};
-            }
-            dm = fmax(dm, fmax(fabs(rv[i][j].x - old.x), fabs(rv[i][j].y - old.y)));
-          }
-      }
-      for (int off = 32; off > 0; off >>= 1) dm = fmax(dm, __shfl_xor(dm, off, 64));
-      if (lane == 0) red[wave] = dm;
-      __syncthreads();
-      for (int k2 = 0; k2 < NW; ++k2) drift = fmax(drift, red[k2]);
-      counter = 0;
-      n_ref += 1;
-    }
+    due = MIXED && K > 0 && counter >= K;  // uniform: rebuild rho in FP64 between chunks
     __syncthreads();  // staging buffers and tables are reused by the next chunk
     m0 += len;
   }
@@ -570,6 +531,25 @@ __global__ __launch_bounds__(NT, NT >= 1024 ? 4 : WV) void k_run(const DevSys* _
           }
         }
       }
+  }
+  if (!(MIXED && K > 0 && counter >= K)) break;
+  __syncthreads();  // the running rho is in the state, for the drift check
+  const double* rfix = XTRA && S->n_fixed > 0 ? S->rho_fix : nullptr;
+  double dm = run_rebuild<DIM, NW>(S, lpos, lq, n0, lds + L.ctab, L.rtile, L.rbytes, rfix, rho);
+  if constexpr (LAY) {
+    __syncthreads();
+    if (lay)
+      dm = fmax(dm, run_rebuild<DIM, NW>(S, lpos + size_t(n0) * DIM, lq + n0, n - n0, lds + L.ctab, L.rtile, L.rbytes,
+                                         rfix ? S->rho_fix1 : nullptr, rho1));
+  }
+  for (int off = 32; off > 0; off >>= 1) dm = fmax(dm, __shfl_xor(dm, off, 64));
+  if (lane == 0) red[wave] = dm;
+  __syncthreads();
+  for (int k2 = 0; k2 < NW; ++k2) drift = fmax(drift, red[k2]);
+  __syncthreads();
+  counter = 0;
+  n_ref += 1;
+  if (m0 >= n_steps) break;
   }
   for (int i = tid; i < n * DIM; i += NT) spos[i] = lpos[i];
   if (tid == 0) {
@@ -603,7 +583,6 @@ size_t run_layout(const LaunchBatch& b, int ch, RunLds& L) {
   constexpr int NW = NT / 64;
   const size_t tbl = size_t(2 * b.max_nm + 1);
   const size_t mtab = 2 * DIM * tbl * sizeof(cplx<R>);                 // one move's tables
-  const size_t rpart = DIM * tbl * sizeof(cplx<double>);               // one rebuild particle
   size_t o = up16(size_t(b.max_particles) * DIM * 8);
   L.q = uint32_t(o);
   o = up16(o + size_t(b.max_particles) * 8);
@@ -619,7 +598,7 @@ size_t run_layout(const LaunchBatch& b, int ch, RunLds& L) {
     o = up16(o + size_t(b.max_wtab) * sizeof(R));
   }
   L.ctab = uint32_t(o);
-  const size_t ctab = std::max(size_t(ch) * mtab, size_t(TILE_P) * rpart);
+  const size_t ctab = std::max(size_t(ch) * mtab, MIXED ? rho_lds(b, TILE_MIN) : 0);
   o = up16(o + ctab);
   L.sn = uint32_t(o);
   o = up16(o + size_t(ch) * DIM * 8);
@@ -648,19 +627,9 @@ size_t run_layout(const LaunchBatch& b, int ch, RunLds& L) {
   }
   L.ch = ch;
   // between chunks everything from ctab on holds per-chunk data only, so the
-  // rebuild tiles may fill all of it; even (the tiles interleave particle pairs)
-  L.rtile = int(std::min<size_t>((o - L.ctab) / rpart, 64)) & ~1;
-  // Between chunks the tables and the staging area (everything from ctab on:
-  // per-chunk data only) are free: the mixed form's rebuild keeps the running
-  // rho there (for the drift check) when it fits beside tiles of at least
-  // TILE_P particles, instead of a round trip through HBM.
-  L.rcopy = 0;
-  const size_t rcopy = size_t(SPT) * NT * SEG * sizeof(cplx<double>);
-  const size_t region = o - L.ctab;
-  if (MIXED && region >= rcopy + size_t(TILE_P) * rpart) {
-    L.rcopy = uint32_t((o - rcopy) & ~size_t(15));
-    L.rtile = int(std::min<size_t>((L.rcopy - L.ctab) / rpart, 64)) & ~1;
-  }
+  // rebuild's tables may fill all of it
+  L.rtile = rho_tile(b, o - L.ctab);
+  L.rbytes = uint32_t(o - L.ctab);
   return o;
 }
 
