@@ -3,18 +3,26 @@
 // grid lookup, a few cubic polynomials, and the multiplication of the 64
 // blip functions that are nonzero at the point by every orbital's
 // coefficients, which the paper sends through 64-element BLAS calls one
-// point at a time, Sec. 5.3).  Here one wave serves one point:
+// point at a time, Sec. 5.3).  Here one wave serves one point and a slice of
+// the orbitals:
 //   - lane p < 64 finds grid point p of the 4 x 4 x 4 window around the
 //     point and forms its blip product, the product's Cartesian gradient and
-//     its Laplacian (five weights), parked in LDS with the row index;
-//   - every lane then streams the 64 coefficient rows (orbital index
-//     fastest, so a wave reads 1 KiB of one row per 16-byte load) and
-//     accumulates value, gradient and Laplacian of two orbitals per chunk of
-//     128 orbitals.
+//     its Laplacian (five weights), kept in registers with the row index;
+//   - the wave then streams the 64 coefficient rows (orbital index fastest),
+//     each row's weights read from their lane into scalar registers, and
+//     accumulates value, gradient and Laplacian of the lane's orbitals.
+//     (Read back from LDS, a row's weights cost more LDS cycles, 20 per row
+//     and wave, than their multiply-adds on four orbitals per lane.)
 // The work is a gather of 64 n_orb coefficients per point with 5 FMAs per
-// coefficient: bound by memory (HBM, or the 256 MB last-level cache when the
-// coefficient set fits it), not by arithmetic, and not a dense contraction
-// (each point takes its own 64 rows).
+// coefficient, not a dense contraction (each point takes its own 64 rows),
+// bound by where the rows come from.  Points in any order take every row from
+// the last-level cache or HBM (262 KB per point at 512 orbitals).  A large batch
+// over a coefficient set beyond the L2s is therefore served in the order of
+// the points' places on the grid (bricks of BRICK^3 cells, each L2 taking a
+// contiguous range), so that the points that share a row (64 windows of the
+// grid hold it) find it in the L2: 65,536 points of 512 orbitals on a 40^3 grid
+// take 1.04 ms (16.6 TB/s of rows) where they took 2.48 ms (7.0 TB/s, weights
+// read from LDS).  The multiply-adds alone are 0.3 ms.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -66,46 +74,68 @@ __device__ __forceinline__ void blip_fn(double x, double& f, double& f1, double&
   }
 }
 
-struct __align__(16) BlipW {
-  double b, gx, gy, gz, l;
-  long long row;  // coefficient row (grid point) index
-};
+constexpr int BLIP_WAVES = 4;  // waves per workgroup
+constexpr int BRICK = 4;       // cells along each side of a brick (ordering of large batches)
+constexpr int BRICKS_MAX = 16384;
 
-constexpr int BLIP_WAVES = 4;  // points (waves) per workgroup
+__device__ __forceinline__ double lane_value(double v, int r) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), r),
+                          __builtin_amdgcn_readlane(__double2loint(v), r));
+}
+
+// A point's grid coordinates x_d = n_d s_d, s wrapped into [0, 1).
+__device__ __forceinline__ void grid_coords(const BlipK& K, const double* __restrict__ pos, size_t p, double* x) {
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    double s = 0.0;
+#pragma unroll
+    for (int e = 0; e < 3; ++e) s = fma(pos[p * 3 + e], K.ainv[e * 3 + d], s);
+    s -= floor(s);
+    x[d] = s * K.n[d];
+  }
+}
 
 // VW = 2: orbital pairs read as 16-byte loads (n_orb even); 1: single loads.
-template <int VW, bool DER>
-__global__ __launch_bounds__(64 * BLIP_WAVES) void k_blip(BlipK K, const double* __restrict__ coef, int n_pts,
-                                                            const double* __restrict__ pos, double* __restrict__ val,
-                                                            double* __restrict__ grad, double* __restrict__ lap) {
-  __shared__ BlipW wts[BLIP_WAVES][64];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int p = blockIdx.x * BLIP_WAVES + wave;
-  if (p >= n_pts) return;  // uniform per wave; no block-level barrier below
-  BlipW* W = wts[wave];
+// NV: vectors of VW orbitals per lane; a wave serves 64 VW NV orbitals of one
+// point and `slices` waves (consecutive, so that they run together) all of them.
+// order: NULL (points p_lo .. p_hi - 1 in turn), or the points' order; those
+// from p_hi on are left to a later launch (their outputs hold the order).
+template <int VW, int NV, bool DER>
+__global__ __launch_bounds__(64 * BLIP_WAVES, 4) void k_blip(BlipK K, const double* __restrict__ coef, int p_lo, int p_hi,
+                                                            int n_items, int slices,
+                                                            const int* order, const double* __restrict__ pos,
+                                                            double* val, double* grad, double* lap) {
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
+  int blk = blockIdx.x;
+  if (order) {
+    // consecutive workgroups go to the eight L2s in turn: give each a
+    // contiguous range (the grid is a multiple of 8)
+    const int per = gridDim.x / 8;
+    blk = (blk & 7) * per + (blk >> 3);
+  }
+  const int item = blk * BLIP_WAVES + wave;
+  if (item >= n_items) return;  // uniform per wave; no block-level barrier below
+  const int it = item / slices, slice = item - it * slices;
+  const int p = order ? __builtin_amdgcn_readfirstlane(order[it]) : p_lo + it;
+  if (p >= p_hi) return;
+  const int n_orb = K.n_orb;
+  double wb, wx = 0.0, wy = 0.0, wz = 0.0, wl = 0.0;
+  uint64_t row;  // byte offset of the lane's coefficient row
   {
     double x[3];
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-      double s = 0.0;
-#pragma unroll
-      for (int e = 0; e < 3; ++e) s = fma(pos[size_t(p) * 3 + e], K.ainv[e * 3 + d], s);
-      s -= floor(s);
-      x[d] = s * K.n[d];
-    }
+    grid_coords(K, pos, size_t(p), x);
     const int a[3] = {lane >> 4, (lane >> 2) & 3, lane & 3};
     double f[3], f1[3], f2[3];
-    long long idx[3];
+    int idx[3];
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
       const double fl = floor(x[d]);
-      const long long g = (long long)fl - 1 + a[d];  // grid points floor(x) - 1 .. floor(x) + 2
+      const int g = int(fl) - 1 + a[d];  // grid points floor(x) - 1 .. floor(x) + 2
       blip_fn(x[d] - double(g), f[d], f1[d], f2[d]);
-      long long gw = g % K.n[d];
+      const int gw = g % K.n[d];
       idx[d] = gw < 0 ? gw + K.n[d] : gw;
     }
-    BlipW w;
-    w.b = f[0] * f[1] * f[2];
+    wb = f[0] * f[1] * f[2];
     if (DER) {
       const double dx[3] = {f1[0] * f[1] * f[2], f[0] * f1[1] * f[2], f[0] * f[1] * f1[2]};
       // second derivatives in x: diagonal and mixed
@@ -114,60 +144,181 @@ __global__ __launch_bounds__(64 * BLIP_WAVES) void k_blip(BlipK K, const double*
       double g[3];
 #pragma unroll
       for (int e = 0; e < 3; ++e) g[e] = fma(K.J[e * 3 + 2], dx[2], fma(K.J[e * 3 + 1], dx[1], K.J[e * 3] * dx[0]));
-      w.gx = g[0];
-      w.gy = g[1];
-      w.gz = g[2];
-      w.l = fma(K.M[0], h00, fma(K.M[1], h11, fma(K.M[2], h22,
-            2.0 * fma(K.M[3], h01, fma(K.M[4], h02, K.M[5] * h12)))));
-    } else {
-      w.gx = w.gy = w.gz = w.l = 0.0;
+      wx = g[0];
+      wy = g[1];
+      wz = g[2];
+      wl = fma(K.M[0], h00, fma(K.M[1], h11, fma(K.M[2], h22,
+           2.0 * fma(K.M[3], h01, fma(K.M[4], h02, K.M[5] * h12)))));
     }
-    w.row = (idx[0] * K.n[1] + idx[1]) * K.n[2] + idx[2];
-    W[lane] = w;
+    row = ((uint64_t(idx[0]) * uint32_t(K.n[1]) + uint32_t(idx[1])) * uint32_t(K.n[2]) + uint32_t(idx[2])) * uint32_t(n_orb) * 8;
   }
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  const int n_orb = K.n_orb;
   const size_t out0 = size_t(p) * n_orb;
-  for (int o = VW * lane; o < n_orb; o += 64 * VW) {
-    double v[VW], gx[VW], gy[VW], gz[VW], l[VW];
+  constexpr int SLICE = 64 * VW * NV;
+  for (int o0 = slice * SLICE; o0 < n_orb; o0 += slices * SLICE) {
+    // opaque per pass: 640 broadcast registers are not to be kept for a next one
+    asm volatile("" : "+v"(wb), "+v"(wx), "+v"(wy), "+v"(wz), "+v"(wl));
+    double v[NV][VW], gx[NV][VW], gy[NV][VW], gz[NV][VW], l[NV][VW];
+    int oo[NV];  // the lane's orbitals (clamped: every load is in bounds)
 #pragma unroll
-    for (int c = 0; c < VW; ++c) v[c] = gx[c] = gy[c] = gz[c] = l[c] = 0.0;
-#pragma unroll 8
-    for (int r = 0; r < 64; ++r) {
-      const BlipW w = W[r];
-      const double* src = coef + size_t(w.row) * n_orb + o;
-      double a[VW];
-      if (VW == 2) {
-        const double2 t = *reinterpret_cast<const double2*>(src);
-        a[0] = t.x;
-        a[VW - 1] = t.y;
-      } else {
-        a[0] = src[0];
-      }
+    for (int i = 0; i < NV; ++i) {
+      const int o = o0 + (i * 64 + lane) * VW;
+      oo[i] = o < n_orb ? o : 0;
 #pragma unroll
-      for (int c = 0; c < VW; ++c) {
-        v[c] = fma(w.b, a[c], v[c]);
-        if (DER) {
-          gx[c] = fma(w.gx, a[c], gx[c]);
-          gy[c] = fma(w.gy, a[c], gy[c]);
-          gz[c] = fma(w.gz, a[c], gz[c]);
-          l[c] = fma(w.l, a[c], l[c]);
+      for (int c = 0; c < VW; ++c) v[i][c] = gx[i][c] = gy[i][c] = gz[i][c] = l[i][c] = 0.0;
+    }
+    constexpr int RB = 8;  // rows in flight
+#pragma unroll 1
+    for (int r0 = 0; r0 < 64; r0 += RB) {
+      double a[RB][NV][VW];
+#pragma unroll
+      for (int r = 0; r < RB; ++r) {
+        const uint64_t at = uint64_t(uint32_t(__builtin_amdgcn_readlane(int(row >> 32), r0 + r))) << 32 |
+                            uint32_t(__builtin_amdgcn_readlane(int(uint32_t(row)), r0 + r));
+        const double* src = reinterpret_cast<const double*>(reinterpret_cast<const char*>(coef) + at);
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+          if (VW == 2) {
+            const double2 t = *reinterpret_cast<const double2*>(src + oo[i]);
+            a[r][i][0] = t.x;
+            a[r][i][VW - 1] = t.y;
+          } else {
+            a[r][i][0] = src[oo[i]];
+          }
         }
       }
-    }
 #pragma unroll
-    for (int c = 0; c < VW; ++c) {
-      val[out0 + o + c] = v[c];
-      if (DER) {
-        grad[3 * out0 + o + c] = gx[c];
-        grad[3 * out0 + n_orb + o + c] = gy[c];
-        grad[3 * out0 + 2 * size_t(n_orb) + o + c] = gz[c];
-        lap[out0 + o + c] = l[c];
+      for (int r = 0; r < RB; ++r) {
+        const double sb = lane_value(wb, r0 + r);
+        double sx = 0.0, sy = 0.0, sz = 0.0, sl = 0.0;
+        if (DER) {
+          sx = lane_value(wx, r0 + r);
+          sy = lane_value(wy, r0 + r);
+          sz = lane_value(wz, r0 + r);
+          sl = lane_value(wl, r0 + r);
+        }
+#pragma unroll
+        for (int i = 0; i < NV; ++i)
+#pragma unroll
+          for (int c = 0; c < VW; ++c) {
+            v[i][c] = fma(sb, a[r][i][c], v[i][c]);
+            if (DER) {
+              gx[i][c] = fma(sx, a[r][i][c], gx[i][c]);
+              gy[i][c] = fma(sy, a[r][i][c], gy[i][c]);
+              gz[i][c] = fma(sz, a[r][i][c], gz[i][c]);
+              l[i][c] = fma(sl, a[r][i][c], l[i][c]);
+            }
+          }
       }
     }
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+      const int o = o0 + (i * 64 + lane) * VW;
+      if (o < n_orb)
+#pragma unroll
+        for (int c = 0; c < VW; ++c) {
+          val[out0 + o + c] = v[i][c];
+          if (DER) {
+            grad[3 * out0 + o + c] = gx[i][c];
+            grad[3 * out0 + n_orb + o + c] = gy[i][c];
+            grad[3 * out0 + 2 * size_t(n_orb) + o + c] = gz[i][c];
+            lap[out0 + o + c] = l[i][c];
+          }
+        }
+    }
   }
+}
+
+// ---- ordering of a large batch by brick: a counting sort ----------------------
+
+struct Bricks {
+  int n[3];  // bricks along each axis
+  int total;
+};
+
+__device__ __forceinline__ int brick_of(const BlipK& K, const Bricks& B, const double* __restrict__ pos, size_t p) {
+  double x[3];
+  grid_coords(K, pos, p, x);
+  int b[3];
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    // (a NaN position converts to some integer: clamped, any brick will do)
+    const int c = int(x[d]) / BRICK;
+    b[d] = min(max(c, 0), B.n[d] - 1);
+  }
+  return (b[0] * B.n[1] + b[1]) * B.n[2] + b[2];
+}
+
+__global__ void k_brick_zero(int* count, int n) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n) count[i] = 0;
+}
+
+__global__ void k_brick_count(BlipK K, Bricks B, const double* __restrict__ pos, int n_pts, int* count) {
+  const int p = blockIdx.x * blockDim.x + threadIdx.x;
+  if (p < n_pts) atomicAdd(&count[brick_of(K, B, pos, size_t(p))], 1);
+}
+
+// Counts to first places, by one workgroup of 1024.
+__global__ __launch_bounds__(1024) void k_brick_scan(int* count, int n) {
+  __shared__ int part[1024];
+  const int per = (n + 1023) / 1024, i0 = threadIdx.x * per, i1 = min(i0 + per, n);
+  int s = 0;
+  for (int i = i0; i < i1; ++i) s += count[i];
+  part[threadIdx.x] = s;
+  __syncthreads();
+  for (int off = 1; off < 1024; off <<= 1) {
+    const int t = int(threadIdx.x) >= off ? part[threadIdx.x - off] : 0;
+    __syncthreads();
+    part[threadIdx.x] += t;
+    __syncthreads();
+  }
+  int first = part[threadIdx.x] - s;
+  for (int i = i0; i < i1; ++i) {
+    const int c = count[i];
+    count[i] = first;
+    first += c;
+  }
+}
+
+// (points of one brick come in any order: no output depends on it)
+__global__ void k_brick_place(BlipK K, Bricks B, const double* __restrict__ pos, int n_pts, int* first, int* order) {
+  const int p = blockIdx.x * blockDim.x + threadIdx.x;
+  if (p < n_pts) order[atomicAdd(&first[brick_of(K, B, pos, size_t(p))], 1)] = p;
+}
+
+// One launch over `count` points (order: of all of them; else p_lo, p_lo + 1, ...).
+// Vectors per lane: two where the orbitals fill them (the weights' broadcast, ten
+// lane reads per row, is shared by more orbitals), one for few points or orbitals
+// (more waves).
+void blip_launch(const BlipK& K, bool vec, bool der, const double* coef, int p_lo, int p_hi, int count,
+                 const int* order, const double* pos, double* val, double* grad, double* lap, hipStream_t s) {
+  const int vw = vec ? 2 : 1;
+  const bool wide = K.n_orb >= 128 * vw && count >= 2048;
+  const int per = 64 * vw * (wide ? 2 : 1);
+  const int slices = (K.n_orb + per - 1) / per;
+  const long long items = (long long)count * slices;
+  // several passes over the orbitals per wave where the items would not fit the grid
+  const int sl = items > (1ll << 30) ? 1 : slices;
+  const int n_items = count * sl;
+  int grid = (n_items + BLIP_WAVES - 1) / BLIP_WAVES;
+  if (order) grid = (grid + 7) & ~7;
+#define EW_BLIP(VW, NV, DER)                                                                                          \
+  hipLaunchKernelGGL((k_blip<VW, NV, DER>), dim3(grid), dim3(64 * BLIP_WAVES), 0, s, K, coef, p_lo, p_hi, n_items, sl, \
+                     order, pos, val, grad, lap)
+  if (vec) {
+    if (wide) {
+      if (der) EW_BLIP(2, 2, true); else EW_BLIP(2, 2, false);
+    } else {
+      if (der) EW_BLIP(2, 1, true); else EW_BLIP(2, 1, false);
+    }
+  } else {
+    if (wide) {
+      if (der) EW_BLIP(1, 2, true); else EW_BLIP(1, 2, false);
+    } else {
+      if (der) EW_BLIP(1, 1, true); else EW_BLIP(1, 1, false);
+    }
+  }
+#undef EW_BLIP
 }
 
 }  // namespace
@@ -260,18 +411,40 @@ ewald_status ewald_blip_eval_batch(const ewald_blip* b, const double* coef, int 
   std::memcpy(K.ainv, b->ainv, sizeof K.ainv);
   std::memcpy(K.J, b->J, sizeof K.J);
   std::memcpy(K.M, b->M, sizeof K.M);
-  const dim3 grid_dim((n_points + ewald::BLIP_WAVES - 1) / ewald::BLIP_WAVES);
-  const dim3 block(64 * ewald::BLIP_WAVES);
   hipStream_t s = static_cast<hipStream_t>(stream);
   const bool der = grad != nullptr;
-  if (vec && der)
-    hipLaunchKernelGGL((ewald::k_blip<2, true>), grid_dim, block, 0, s, K, coef, n_points, pos, val, grad, lap);
-  else if (vec)
-    hipLaunchKernelGGL((ewald::k_blip<2, false>), grid_dim, block, 0, s, K, coef, n_points, pos, val, grad, lap);
-  else if (der)
-    hipLaunchKernelGGL((ewald::k_blip<1, true>), grid_dim, block, 0, s, K, coef, n_points, pos, val, grad, lap);
-  else
-    hipLaunchKernelGGL((ewald::k_blip<1, false>), grid_dim, block, 0, s, K, coef, n_points, pos, val, grad, lap);
+  // Ordered where the coefficients exceed the L2s (4 MB each, and a row that
+  // one of them holds is shared by points that all run there) and the points
+  // are enough for rows to be shared; the order (one int per point and per
+  // brick) sits at the end of `val` until the main launch has read it, and the
+  // points whose values lie there are evaluated last.  16 orbitals at least
+  // keep these few.
+  const double rows = double(b->grid[0]) * b->grid[1] * b->grid[2];
+  ewald::Bricks B;
+  for (int d = 0; d < 3; ++d) B.n[d] = (b->grid[d] + ewald::BRICK - 1) / ewald::BRICK;
+  const bool ordered = rows * b->n_orb * 8.0 > 16e6 && b->n_orb >= 16 && n_points >= 2048 && n_points >= rows / 16 &&
+                       double(B.n[0]) * B.n[1] * B.n[2] <= ewald::BRICKS_MAX;
+  if (ordered) {
+    B.total = B.n[0] * B.n[1] * B.n[2];
+    const size_t ints = size_t(n_points) + size_t(B.total);
+    const int late = int((ints * 4 + size_t(b->n_orb) * 8 - 1) / (size_t(b->n_orb) * 8));  // points that are evaluated last
+    if (late < n_points) {
+      const int p_hi = n_points - late;
+      int* count = reinterpret_cast<int*>(val + size_t(p_hi) * b->n_orb);
+      int* order = count + B.total;
+      const dim3 per_point((n_points + 255) / 256);
+      hipLaunchKernelGGL(ewald::k_brick_zero, dim3((B.total + 255) / 256), dim3(256), 0, s, count, B.total);
+      hipLaunchKernelGGL(ewald::k_brick_count, per_point, dim3(256), 0, s, K, B, pos, n_points, count);
+      hipLaunchKernelGGL(ewald::k_brick_scan, dim3(1), dim3(1024), 0, s, count, B.total);
+      hipLaunchKernelGGL(ewald::k_brick_place, per_point, dim3(256), 0, s, K, B, pos, n_points, count, order);
+      ewald::blip_launch(K, vec, der, coef, 0, p_hi, n_points, order, pos, val, grad, lap, s);
+      ewald::blip_launch(K, vec, der, coef, p_hi, n_points, late, nullptr, pos, val, grad, lap, s);
+    } else {
+      ewald::blip_launch(K, vec, der, coef, 0, n_points, n_points, nullptr, pos, val, grad, lap, s);
+    }
+  } else {
+    ewald::blip_launch(K, vec, der, coef, 0, n_points, n_points, nullptr, pos, val, grad, lap, s);
+  }
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) {
     ewald::set_last_error(std::string("blip launch failed: ") + hipGetErrorString(e));
