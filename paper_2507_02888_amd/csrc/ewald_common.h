@@ -71,28 +71,40 @@ __device__ __forceinline__ cplx<R> rotate_quarter(R c, R s, int q) {
   return (q & 2) ? cplx<R>{-x, -y} : cplx<R>{x, y};
 }
 
+// A constant put into scalar registers where it is used (the asm takes x, the
+// argument at hand, so that it is not moved out of loops).  Left to itself the
+// compiler keeps the series' 17 constants in vector registers across the
+// kernels' main loops: at 128 registers per lane 40 to 100 more were spilled
+// (the derivative sweep with the u term at N = 1024 took 4.9 ms instead of 3.7),
+// and one spill was placed at a loop's exit where no lane is active, so that
+// later phases were built from a stale constant.
+__device__ __forceinline__ double scalar_k(double c, double x) {
+  asm("" : "+s"(c) : "v"(x));
+  return c;
+}
+
 __device__ __forceinline__ cplx<double> turn(double x) {
   double r;
   int q;
   quarter_turns(x, r, q);
   const double th = r * 1.5707963267948966, t2 = th * th;
-  double sp = 2.8114572543455206e-15;
-  sp = fma(sp, t2, -7.6471637318198165e-13);
-  sp = fma(sp, t2, 1.6059043836821613e-10);
-  sp = fma(sp, t2, -2.5052108385441720e-08);
-  sp = fma(sp, t2, 2.7557319223985893e-06);
-  sp = fma(sp, t2, -1.9841269841269841e-04);
-  sp = fma(sp, t2, 8.3333333333333333e-03);
-  sp = fma(sp, t2, -1.6666666666666667e-01);
+  double sp = scalar_k(2.8114572543455206e-15, th);
+  sp = fma(sp, t2, scalar_k(-7.6471637318198165e-13, th));
+  sp = fma(sp, t2, scalar_k(1.6059043836821613e-10, th));
+  sp = fma(sp, t2, scalar_k(-2.5052108385441720e-08, th));
+  sp = fma(sp, t2, scalar_k(2.7557319223985893e-06, th));
+  sp = fma(sp, t2, scalar_k(-1.9841269841269841e-04, th));
+  sp = fma(sp, t2, scalar_k(8.3333333333333333e-03, th));
+  sp = fma(sp, t2, scalar_k(-1.6666666666666667e-01, th));
   sp = fma(sp, t2 * th, th);
-  double cp = -1.5619206968586225e-16;
-  cp = fma(cp, t2, 4.7794773323873853e-14);
-  cp = fma(cp, t2, -1.1470745597729725e-11);
-  cp = fma(cp, t2, 2.0876756987868099e-09);
-  cp = fma(cp, t2, -2.7557319223985891e-07);
-  cp = fma(cp, t2, 2.4801587301587302e-05);
-  cp = fma(cp, t2, -1.3888888888888889e-03);
-  cp = fma(cp, t2, 4.1666666666666667e-02);
+  double cp = scalar_k(-1.5619206968586225e-16, th);
+  cp = fma(cp, t2, scalar_k(4.7794773323873853e-14, th));
+  cp = fma(cp, t2, scalar_k(-1.1470745597729725e-11, th));
+  cp = fma(cp, t2, scalar_k(2.0876756987868099e-09, th));
+  cp = fma(cp, t2, scalar_k(-2.7557319223985891e-07, th));
+  cp = fma(cp, t2, scalar_k(2.4801587301587302e-05, th));
+  cp = fma(cp, t2, scalar_k(-1.3888888888888889e-03, th));
+  cp = fma(cp, t2, scalar_k(4.1666666666666667e-02, th));
   cp = fma(cp, t2, -0.5);
   cp = fma(cp, t2, 1.0);
   return rotate_quarter<double>(cp, sp, q);
@@ -272,7 +284,10 @@ struct Kahan {
 // FP64 form: everything in FP64.  Mixed form: 1/r in FP64 (it carries the
 // close-pair singularity) and the bounded erf part in FP32 (degree 12 or 22)
 // summed with Kahan compensation.
-template <bool MIXED, int PD>
+// FLUSH (mixed form): the compensated sum is moved to FP64 after every two
+// terms (a particle's new and old distance), so that the sum does not depend
+// on how many particles a thread holds.
+template <bool MIXED, int PD, bool FLUSH = false>
 struct PairAcc;
 
 // 1/sqrt(x) for x in (0, r_cut^2]: the hardware estimate refined by one
@@ -289,8 +304,8 @@ __device__ __forceinline__ double rsqrt_pos(double x) {
 // Pair terms are evaluated several at a time (NE = 2 or 4): the four Horner chains interleave
 // (latency hiding) and take their coefficients straight from scalar registers.
 // A term enters iff r2 < r_cut^2; callers pad with r2 = r_cut^2 and q = 0.
-template <int PD>
-struct PairAcc<false, PD> {
+template <int PD, bool FLUSH>
+struct PairAcc<false, PD, FLUSH> {
   double s = 0.0;
   const double* __restrict__ c;  // the polynomial coefficients (system tables, or registers)
   const FrameK& K;
@@ -328,8 +343,8 @@ struct PairAcc<false, PD> {
   __device__ __forceinline__ double value() const { return s; }
 };
 
-template <int PD>
-struct PairAcc<true, PD> {
+template <int PD, bool FLUSH>
+struct PairAcc<true, PD, FLUSH> {
   static constexpr int PF = PD == 16 ? 12 : 22;
   double inv = 0.0;
   Kahan erfpart;
@@ -365,6 +380,10 @@ struct PairAcc<true, PD> {
       const double qe = r2[e] < rc2 ? q[e] : 0.0;
       inv = fma(qe, ir[e], inv);
       erfpart.add(float(qe) * (alpha * p[e]));
+      if (FLUSH && (e & 1)) {
+        inv -= erfpart.value();
+        erfpart = Kahan{};
+      }
     }
   }
   __device__ __forceinline__ double value() const { return inv - erfpart.value(); }
@@ -637,7 +656,7 @@ __device__ __forceinline__ double real_move(const double* sn, const double* so, 
 // LAY (a layered system when `lay`): partners in the other plane (mobile
 // j >= n0 against k, or an ion's plane) are dz2 further apart in r^2.
 template <int DIM, bool MIXED, int PD, int NT, int PPR, bool ORTHO, bool XTRA, bool UJ = false, bool UD = false,
-          bool LAY = false>
+          bool LAY = false, bool FLUSH = false>
 __device__ __forceinline__ double real_move_own(const double* sn, const double* so, int k,
                                                 const double (&ps)[PPR][DIM], const double (&pq)[PPR],
                                                 const double* lpos, const double* lq, int n,
@@ -646,7 +665,7 @@ __device__ __forceinline__ double real_move_own(const double* sn, const double* 
                                                 const int* psp = nullptr, int sk = 0,
                                                 UOut<DIM>* uo = nullptr, bool lay = false, int n0 = 0,
                                                 double dz2 = 0.0) {
-  PairAcc<MIXED, PD> pr(c64, c32, K);
+  PairAcc<MIXED, PD, FLUSH> pr(c64, c32, K);
   const int n_cand = S->n_cand;
   const double rc2 = S->rc2;
   const int lk = k >= n0 ? 1 : 0;
@@ -741,42 +760,8 @@ __device__ __forceinline__ double real_move_own(const double* sn, const double* 
   return pr.value();
 }
 
-// Sum NV values over a workgroup of NT threads; the result is valid in
-// thread 0.  red must hold NV * NT / 64 doubles.
-template <int NV, int NT = BLOCK>
-__device__ __forceinline__ void block_sum(double (&v)[NV], double* red) {
-#pragma unroll
-  for (int i = 0; i < NV; ++i)
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v[i] += __shfl_xor(v[i], off, 64);
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  if (lane == 0)
-#pragma unroll
-    for (int i = 0; i < NV; ++i) red[i * (NT / 64) + wv] = v[i];
-  __syncthreads();
-  if (threadIdx.x == 0)
-#pragma unroll
-    for (int i = 0; i < NV; ++i) {
-      double t = 0.0;
-#pragma unroll
-      for (int k = 0; k < NT / 64; ++k) t += red[i * (NT / 64) + k];
-      v[i] = t;
-    }
-}
-
-// Wave64 sum with DPP row operations (no LDS round trips); the total lands in
-// lane 63.  Steps: swap neighbours, swap pairs, mirror half rows, mirror rows
-// (every lane of a row then holds the row sum), then add row 0 into row 1 and
-// row 2 into row 3 (row_bcast15), and rows 0-1 into rows 2-3 (row_bcast31).
-template <int CTRL, int ROWS>
-__device__ __forceinline__ double dpp_take(double v) {
-  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROWS, 0xF, false);
-  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROWS, 0xF, false);
-  return __hiloint2double(hi, lo);
-}
-
-// Sum over each row of 16 lanes with DPP moves whose every lane has a source
-// (no previous value to preserve); every lane of a row ends with the row sum.
+// A double moved between the lanes of a row of 16 by a DPP pattern in which every
+// lane has a source (no previous value to preserve).
 template <int CTRL>
 __device__ __forceinline__ double dpp_all(double v) {
   const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xF, 0xF, true);
@@ -784,22 +769,61 @@ __device__ __forceinline__ double dpp_all(double v) {
   return __hiloint2double(hi, lo);
 }
 
-__device__ __forceinline__ double row_sum16(double v) {
-  v += dpp_all<0xB1>(v);   // quad_perm [1,0,3,2]
-  v += dpp_all<0x4E>(v);   // quad_perm [2,3,0,1]
-  v += dpp_all<0x141>(v);  // row_half_mirror
-  v += dpp_all<0x140>(v);  // row_mirror
-  return v;
+// Sums of N values over each row of 16 lanes, stored at p[0 .. N - 1] (p: the
+// row's place).  Four values go through the row together: a lane hands its
+// neighbour the values that it does not keep, so after two exchanges lane
+// l of a row holds the sum of value l % 4 over its quad, and two rotations add
+// the quads.  That is 75 issue cycles for four values (46 for two) against 37
+// for each by itself.
+template <int N>
+__device__ __forceinline__ void row_sums(const double (&v)[N], int lane, double* p) {
+  const bool odd = lane & 1, upper = lane & 2;
+  auto pair = [&](double a, double b) { return (odd ? b : a) + dpp_all<0xB1>(odd ? a : b); };  // quad_perm [1,0,3,2]
+  auto rest = [&](double x) {
+    x += dpp_all<0x124>(x);  // row_ror 4
+    x += dpp_all<0x128>(x);  // row_ror 8
+    return x;
+  };
+  constexpr int N4 = N & ~3;
+#pragma unroll
+  for (int i = 0; i < N4; i += 4) {
+    const double ab = pair(v[i], v[i + 1]), cd = pair(v[i + 2], v[i + 3]);
+    const double x = rest((upper ? cd : ab) + dpp_all<0x4E>(upper ? ab : cd));  // quad_perm [2,3,0,1]
+    if ((lane & 15) < 4) p[i + (lane & 3)] = x;
+  }
+  if constexpr (N - N4 >= 2) {
+    double x = pair(v[N4], v[N4 + 1]);
+    x = rest(x + dpp_all<0x4E>(x));
+    if ((lane & 15) < 2) p[N4 + (lane & 1)] = x;
+  }
+  if constexpr ((N & 1) != 0) {
+    double x = v[N - 1];
+    x += dpp_all<0xB1>(x);
+    x = rest(x + dpp_all<0x4E>(x));
+    if ((lane & 15) == 0) p[N - 1] = x;
+  }
 }
 
-__device__ __forceinline__ double wave_sum_to_lane63(double v) {
-  v += dpp_take<0xB1, 0xF>(v);   // quad_perm [1,0,3,2]
-  v += dpp_take<0x4E, 0xF>(v);   // quad_perm [2,3,0,1]
-  v += dpp_take<0x141, 0xF>(v);  // row_half_mirror
-  v += dpp_take<0x140, 0xF>(v);  // row_mirror
-  v += dpp_take<0x142, 0xA>(v);  // row_bcast15 into rows 1 and 3
-  v += dpp_take<0x143, 0xC>(v);  // row_bcast31 into rows 2 and 3
-  return v;
+// Sum NV values over a workgroup of NT threads; the result is valid in the
+// first wave.  red must hold NV * NT / 16 doubles.  Rows of 16 lanes by DPP, then
+// one lane per value over the rows: a butterfly of shuffles goes through LDS
+// six times per value, one after the other.
+template <int NV, int NT = BLOCK>
+__device__ __forceinline__ void block_sum(double (&v)[NV], double* red) {
+  static_assert(NV <= 64, "one lane per value");
+  const int lane = threadIdx.x & 63;
+  row_sums<NV>(v, lane, red + (threadIdx.x >> 4) * NV);
+  __syncthreads();
+  if (threadIdx.x < 64) {
+    double t = 0.0;
+    if (lane < NV)
+#pragma unroll
+      for (int r = 0; r < NT / 16; ++r) t += red[r * NV + lane];
+#pragma unroll
+    for (int i = 0; i < NV; ++i)
+      v[i] = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(t), i),
+                              __builtin_amdgcn_readlane(__double2loint(t), i));
+  }
 }
 
 // Phase tables: per dimension d one row of tbl = 2 nm + 1 complex entries,

@@ -40,6 +40,7 @@ namespace ewald {
 // stored in the walker state.
 // UJ: the Jastrow value also takes the two-body polynomial term u over the
 // mobile pairs (Sec. 2.3, Eq. (8)).
+constexpr int RED_ENERGY = 48;  // LDS doubles for k_energy's reduction
 template <int DIM, int PD, bool ORTHO, bool UJ>
 __global__ __launch_bounds__(BLOCK, 4) void k_energy(const DevSys* __restrict__ systems,
                                                   const DevWalker* __restrict__ walkers,
@@ -57,9 +58,9 @@ __global__ __launch_bounds__(BLOCK, 4) void k_energy(const DevSys* __restrict__ 
   double* rho = reinterpret_cast<double*>(st + HDR_BYTES + walker_pos_bytes(n, DIM));
   // LDS: the phase-table tiles first, then (in the same space) the
   // pair loop's positions and charges
-  double* red = smem;                        // [4 * 4]
-  char* tabs = reinterpret_cast<char*>(smem + 16);
-  double* lpos = smem + 16;                  // [DIM][lds_pos] in the pair loop's geometry (planar:
+  double* red = smem;                        // [16 rows][3]
+  char* tabs = reinterpret_cast<char*>(smem + RED_ENERGY);
+  double* lpos = smem + RED_ENERGY;                  // [DIM][lds_pos] in the pair loop's geometry (planar:
                                              // lanes reading consecutive particles hit consecutive banks)
   double* lq = lpos + lds_pos * DIM;         // [n]
 
@@ -234,7 +235,7 @@ __global__ __launch_bounds__(BLOCK, 4) void k_energy(const DevSys* __restrict__ 
 // ---------------------------------------------------------------------------
 // Per-step calls: move delta (optionally folding in the previous move's
 // accept) and accept.
-constexpr int RED_DELTA = 48;  // LDS doubles for k_delta's reduction: up to 12 sums x 4 waves
+constexpr int RED_DELTA = 192;  // LDS doubles for k_delta's reduction: up to 12 sums x 16 rows
 
 // rho += q (e_new - e_old) for an accepted move: the difference and its
 // product with q in the form's precision, the sum in FP64 (the per-step
@@ -346,7 +347,7 @@ __global__ __launch_bounds__(BLOCK, 4) void k_delta(const DevSys* __restrict__ s
   const bool lay = DIM == 2 && S->n_layers > 1;
   const size_t plane = 2 * size_t(SEG) * nseg;
   const int lp = lay && acc && pk >= S->n0 ? 1 : 0;
-  double* red = smem;  // [NV][4], NV <= RED_DELTA / 4
+  double* red = smem;  // [16 rows][NV]
   cplx<R>* to = reinterpret_cast<cplx<R>*>(smem + RED_DELTA);
   cplx<R>* tn = to + DIM * tbl;
   cplx<R>* tpo = tn + DIM * tbl;  // the accepted move's old and new position
@@ -546,7 +547,7 @@ __global__ __launch_bounds__(BLOCK, 4) void k_delta(const DevSys* __restrict__ s
   const double q2 = qk * qk;
   constexpr int NP = DER ? 3 + DIM : 2;         // energy, J, and the p-term derivative sums
   constexpr int NV = NP + (UJ && DER ? DIM + 1 : 0);  // and the u term's gradient (frame axes) and Laplacian
-  static_assert(NV * (BLOCK / 64) <= RED_DELTA, "reduction area too small");
+  static_assert(NV * (BLOCK / 16) <= RED_DELTA, "reduction area too small");
   double v[NV];
   v[0] = q2 * (MIXED ? accE32.value() : accE64) + qk * er;
   if (lay) v[0] += 2.0 * qk * (MIXED ? accX32.value() : accX64);
@@ -703,7 +704,7 @@ template <int DIM, int PD, bool ORTHO, bool UJ>
 int energy_inst(const LaunchBatch& b, const double* pos, char* state, double* energy, double* jastrow,
                 void* stream) {
   const int lds_pos = even(b.max_particles);
-  const size_t head = 16 * 8, pairs = size_t(lds_pos) * (DIM + 1) * 8;
+  const size_t head = RED_ENERGY * 8, pairs = size_t(lds_pos) * (DIM + 1) * 8;
   auto* kern = k_energy<DIM, PD, ORTHO, UJ>;
   // phase-table tiles (sharing their LDS with the pair loop's positions) as
   // large as LDS allows without lowering the workgroups per CU that

@@ -28,12 +28,16 @@ namespace ewald {
 //   - each wave reduces its partial sums per row of 16 lanes with DPP and
 //     parks the four row sums in LDS; the cross-row sums of the chunk are
 //     formed after the chunk, in a fixed order.
+// A chunk is staged by the first wave alone (a lane per move; what a move needs
+// of the earlier ones comes from ballots and lane reads), while the last wave
+// forms the outputs of the chunk before: three barriers a chunk, and no
+// lane waits through a loop of dependent LDS reads.
 // A chunk ends early after a move that brings the accept counter to K, so the
 // FP64 rebuild of the mixed form runs between chunks.
 struct RunLds {
   // byte offsets into dynamic LDS; positions start at 0
-  uint32_t q, red, wtab, ctab, sn, so, xn, xo, c2q, part, k, acc, cnt;
-  uint32_t wtab2, part2;  // Jastrow derivatives: a |G|^2 per shell, and the per-move partial sums
+  uint32_t q, red, wtab, ctab, sn, so, xn, xo, c2q, mq, part, k, acc, info;
+  uint32_t wtab2;  // Jastrow derivatives: a |G|^2 per shell
   uint32_t rbytes;  // LDS bytes that the rebuild between chunks may use, from ctab on
   uint32_t next;   // queue mode: the next walker's index, broadcast to the workgroup
   int ch;     // moves per chunk
@@ -109,6 +113,12 @@ __global__ __launch_bounds__(NT, NT >= 1024 ? 4 : WV) void k_run(const DevSys* _
   constexpr bool JAS = JM > 0, DER = JM == 2 || JM == 4, UJ = JM >= 3;
   constexpr int NDP = DIM + 1;               // p-term derivative sums per move: S_0 .. S_{DIM-1}, L
   constexpr int NDV = UJ ? 2 * NDP : NDP;    // plus the u term's gradient (frame axes) and Laplacian
+  constexpr int NE = JAS ? 2 : 1;            // dE, dJ
+  // mixed form, 512 x 2: the FP32 segment sums and a particle's two pair terms
+  // are added up in FP64, so that the choice between this shape and 1024 x 1
+  // (one segment and particle per thread) does not show in the results
+  constexpr bool FLUSH = MIXED && NT == 512 && SPT == 2;
+  constexpr int NV = NE + (DER ? NDV : 0);   // sums per move
   using R = typename std::conditional<MIXED, float, double>::type;
   using WT = R;          // the mixed form multiplies weights with FP32 terms
   using WT2 = cplx<WT>;  // (weight, Jastrow coefficient)
@@ -145,12 +155,12 @@ __global__ __launch_bounds__(NT, NT >= 1024 ? 4 : WV) void k_run(const DevSys* _
   double* st_xn = reinterpret_cast<double*>(lds + L.xn);  // sn, so in the real-space geometry (ORTHO)
   double* st_xo = reinterpret_cast<double*>(lds + L.xo);
   double* st_c2q = reinterpret_cast<double*>(lds + L.c2q);  // 2 / q_k of each move (0 for q_k = 0)
-  double* st_part = reinterpret_cast<double*>(lds + L.part);  // [CH][NW][4 rows][2]
-  double* st_part2 = reinterpret_cast<double*>(lds + L.part2);  // DER: [CH][NW][4 rows][NDV]
+  double* st_mq = reinterpret_cast<double*>(lds + L.mq);        // q_k of each move
+  double* st_part = reinterpret_cast<double*>(lds + L.part);  // [CH][NW][4 rows][NV]
   WT* ltab2 = reinterpret_cast<WT*>(lds + L.wtab2);              // DER: a |G|^2 per shell
-  int* st_k = reinterpret_cast<int*>(lds + L.k);
+  int* st_k = reinterpret_cast<int*>(lds + L.k);        // [2][CH]: the chunk before is still being put out
   int* st_acc = reinterpret_cast<int*>(lds + L.acc);
-  int* st_cnt = reinterpret_cast<int*>(lds + L.cnt);
+  int* st_info = reinterpret_cast<int*>(lds + L.info);  // moves of the chunk, its accepts
 
   for (int i = tid; i < n * DIM; i += NT) lpos[i] = spos[i];
   for (int i = tid; i < n; i += NT) lq[i] = S->mobile_q[i];
@@ -188,11 +198,14 @@ __global__ __launch_bounds__(NT, NT >= 1024 ? 4 : WV) void k_run(const DevSys* _
   const float* c32 = CV ? cf32 : S->p32;
   FrameK fk{};  // with 1024 threads the constants are read where they are used
   if (CV) fk = frame_k_vector(S);
+  // segments start with the last thread (particles with the first), so that the
+  // waves with a second segment and those with a second particle differ
+  const int ts = NT - 1 - tid;
   uint32_t an[SPT];
   uint32_t shp[SPT][SEG / 2];  // two 16-bit shell-table byte offsets per register
 #pragma unroll
   for (int i = 0; i < SPT; ++i) {
-    const int s = tid + i * NT;
+    const int s = ts + i * NT;
     an[i] = s < nseg ? S->seg_n[s] : 0u;
 #pragma unroll
     for (int j = 0; j < SEG; j += 2) {
@@ -222,7 +235,7 @@ __global__ __launch_bounds__(NT, NT >= 1024 ? 4 : WV) void k_run(const DevSys* _
   cplx<double> rv2[LAY ? SPT : 1][SEG];  // LAY: the second plane
 #pragma unroll
   for (int i = 0; i < SPT; ++i) {
-    const int s = tid + i * NT;
+    const int s = ts + i * NT;
 #pragma unroll
     for (int j = 0; j < SEG; ++j) {
       const size_t g = size_t(j) * nseg + s;
@@ -232,73 +245,124 @@ __global__ __launch_bounds__(NT, NT >= 1024 ? 4 : WV) void k_run(const DevSys* _
     }
   }
 
-  for (bool due = false; m0 < n_steps && !due;) {
-    // ---- stage the chunk: proposals, old positions, accept counts ----
-    const int cnt = min(CH, n_steps - m0);
-    if (tid < cnt) {
-      const size_t idx = size_t(m0 + tid) * n_walkers + w;
-      const int kv = kk[idx];
-      st_k[tid] = (kv < 0 || kv >= n) ? -1 : kv;
-      st_acc[tid] = accept[idx] != 0;
-      double r[DIM], sv[DIM];
+  // ---- stage the chunk from move m1 on (the first wave): proposals, old
+  // positions, accepts, length ----
+  auto stage = [&](int m1, int* skw) {
+    const int cnt = min(CH, n_steps - m1);
+    const bool on = lane < cnt;
+    int k = -1;
+    bool a = false;
+    double sv[DIM];
+#pragma unroll
+    for (int d = 0; d < DIM; ++d) sv[d] = 0.0;
+    if (on) {
+      const size_t idx = size_t(m1 + lane) * n_walkers + w;
+      k = kk[idx];
+      k = (k < 0 || k >= n) ? -1 : k;
+      a = k >= 0 && accept[idx] != 0;
+      double r[DIM];
 #pragma unroll
       for (int d = 0; d < DIM; ++d) r[d] = new_pos[idx * DIM + d];
       to_frac<DIM>(r, S->Ainv, sv);
-#pragma unroll
-      for (int d = 0; d < DIM; ++d) st_sn[tid * DIM + d] = sv[d];
     }
-    __syncthreads();
-    if (tid < cnt) {
-      const int k = st_k[tid];
-      int prev = -1, c = counter;
-      for (int q = 0; q < tid; ++q) {
-        const bool a = st_k[q] >= 0 && st_acc[q] != 0;
-        if (a && st_k[q] == k) prev = q;
-        c += a ? 1 : 0;
-      }
-      if (k >= 0) {
-        double so[DIM];
-#pragma unroll
-        for (int d = 0; d < DIM; ++d) {
-          so[d] = prev >= 0 ? st_sn[prev * DIM + d] : lpos[k * DIM + d];
-          st_so[tid * DIM + d] = so[d];
-        }
-        if (ORTHO) {
-          frame_coords<DIM>(so, S, st_xo + tid * DIM);
-          frame_coords<DIM>(st_sn + tid * DIM, S, st_xn + tid * DIM);
-        }
-        st_c2q[tid] = lq[k] != 0.0 ? 2.0 / lq[k] : 0.0;
-      }
-      st_cnt[tid] = c + ((k >= 0 && st_acc[tid] != 0) ? 1 : 0);  // accepts since the rebuild, after this move
+    const uint64_t accs = __ballot(a);
+    int prev = -1;  // the latest accepted earlier move of the same particle in the chunk
+    for (uint64_t m = accs; m != 0; m &= m - 1) {  // uniform
+      const int q = __builtin_ctzll(m);
+      if (__builtin_amdgcn_readlane(k, q) == k && q < lane) prev = q;
     }
-    __syncthreads();
+    double so[DIM];
+#pragma unroll
+    for (int d = 0; d < DIM; ++d) {
+      const double s_prev = __shfl(sv[d], prev < 0 ? 0 : prev, 64);
+      so[d] = k < 0 ? 0.0 : prev >= 0 ? s_prev : lpos[k * DIM + d];
+    }
     int len = cnt;
-    if (MIXED && K > 0)
-      for (int q = 0; q < cnt; ++q)
-        if (st_cnt[q] >= K) {
-          len = q + 1;
-          break;
-        }
+    if (MIXED && K > 0) {  // the chunk ends with the move that brings the accepts since the rebuild to K
+      const uint64_t full = __ballot(on && counter + int(__popcll(accs & (~0ull >> (63 - lane)))) >= K);
+      if (full != 0) len = __builtin_ctzll(full) + 1;
+    }
+    if (on) {
+      skw[lane] = k;
+      st_acc[lane] = a;
+#pragma unroll
+      for (int d = 0; d < DIM; ++d) {
+        st_sn[lane * DIM + d] = sv[d];
+        st_so[lane * DIM + d] = so[d];
+      }
+      if (ORTHO) {
+        frame_coords<DIM>(so, S, st_xo + lane * DIM);
+        frame_coords<DIM>(sv, S, st_xn + lane * DIM);
+      }
+      const double qk = k >= 0 ? lq[k] : 0.0;
+      st_mq[lane] = qk;
+      st_c2q[lane] = qk != 0.0 ? 2.0 / qk : 0.0;
+    }
+    if (lane == 0) {
+      st_info[0] = len;
+      st_info[1] = int(__popcll(accs & (~0ull >> (64 - len))));
+    }
+  };
+  // ---- outputs of the chunk of len moves from m1 on (the last wave;
+  // cross-row sums in a fixed order) ----
+  auto put_out = [&](int m1, int len, const int* skw) {
+    if (lane >= len) return;
+    const size_t idx = size_t(m1 + lane) * n_walkers + w;
+    const int kq = skw[lane];
+    double sv[NV];
+#pragma unroll
+    for (int d = 0; d < NV; ++d) sv[d] = 0.0;
+    const double* p = st_part + lane * NW * 4 * NV;
+#pragma unroll 8
+    for (int v = 0; v < NW * 4; ++v)
+#pragma unroll
+      for (int d = 0; d < NV; ++d) sv[d] += p[v * NV + d];
+    delta[idx] = kq < 0 ? NAN : sv[0];
+    if (djas) djas[idx] = kq < 0 ? NAN : JAS ? sv[NE - 1] : 0.0;
+    if constexpr (DER) {
+      const double* g = sv + NE;
+      const double qk = kq >= 0 ? lq[kq] : 0.0;
+      double ug[DIM];  // u term gradient in Cartesian axes
+      if (UJ) frame_to_cart<DIM>(g + NDP, ORTHO ? S->Eo : S->El, ug);
+#pragma unroll
+      for (int e2 = 0; e2 < DIM; ++e2) {
+        double gx = 0.0;
+#pragma unroll
+        for (int d = 0; d < DIM; ++d) gx = fma(g[d], S->B[d * 3 + e2], gx);
+        jgrad[idx * DIM + e2] = kq < 0 ? NAN : -2.0 * qk * gx + (UJ ? ug[e2] : 0.0);
+      }
+      jlap[idx] = kq < 0 ? NAN : -2.0 * qk * g[DIM] + 2.0 * qk * qk * S->jlap_c + (UJ ? g[NDV - 1] : 0.0);
+    }
+  };
+  bool more = m0 < n_steps;
+  int* sk = st_k;  // this chunk's moved particles
+  if (more) {
+    if (wave == 0) stage(m0, sk);
+    __syncthreads();
+  }
+  while (more) {
+    const int len = uniform_i(st_info[0]), n_in = uniform_i(st_info[1]);
     // ---- phase tables of every move of the chunk (old, then new position) ----
     // row e: move e / (2 DIM), old (0) or new (1) position, dimension; the
     // tables of a move are [old: DIM rows][new: DIM rows]
-    for (int e = tid; e < len * 2 * DIM; e += NT) {
+    for (int e0 = 0; e0 < len * 2 * DIM; e0 += NT) {  // uniform
+      const int e = e0 + tid;
       const int q = e / (2 * DIM), r = e - q * (2 * DIM);
-      if (st_k[q] >= 0)
+      if (e < len * 2 * DIM && sk[q] >= 0)
         fill_row<R>(ctab + e * tbl, r < DIM ? st_so[q * DIM + r] : st_sn[q * DIM + r - DIM], nm);
     }
     __syncthreads();
 
     // ---- the chunk's moves, no barrier ----
     for (int mm = 0; mm < len; ++mm) {
-      const int k = uniform_i(st_k[mm]);  // the move's index, decision and charge are uniform
+      const int k = uniform_i(sk[mm]);  // the move's index, decision and charge are uniform
       double v0 = 0.0, v1 = 0.0;
       double dv[DER ? NDV : 1];  // DER: this thread's S_d and a |G|^2 Re z sums
 #pragma unroll
       for (int d = 0; d < (DER ? NDV : 1); ++d) dv[d] = 0.0;
       if (k >= 0) {  // uniform
         const bool acc = uniform_i(st_acc[mm]) != 0;
-        const double qk = uniform_d(lq[k]);
+        const double qk = uniform_d(st_mq[mm]);
         double sn[DIM], xn[DIM], xo[DIM];  // new (fractional), new and old in the real-space geometry
 #pragma unroll
         for (int d = 0; d < DIM; ++d) {
@@ -312,10 +376,12 @@ __global__ __launch_bounds__(NT, NT >= 1024 ? 4 : WV) void k_run(const DevSys* _
           const cplx<R> uo = tab_at(to, DIM - 1, nm + 1, tbl), un = tab_at(tn, DIM - 1, nm + 1, tbl);
           // t(G) = q^2 [dx (dx + (2/q) rho_x) + dy (dy + (2/q) rho_y)], q^2 applied to the sums
           const R q = R(qk), c2q = R(uniform_d(st_c2q[mm]));
-          const R qa = acc ? q : R(0);
           double accE64 = 0.0, accJ64 = 0.0, accX64 = 0.0;
           Kahan accE32, accJ32, accX32;  // mixed form: FP32 sums per segment, compensated across segments
           if constexpr (LAY) {
+            // rho += q d on an accepted move: the charge times the uniform decision
+            // (0 when rejected, which adds an exact zero)
+            const R qa = acc ? q : R(0);
             // own plane own[], other plane oth[]: the term as below plus the
             // cross-plane sum w_x (rho_o . d); one copy of the loop per plane
             // of the moved particle (uniform), so no per-lane selects
@@ -325,7 +391,7 @@ __global__ __launch_bounds__(NT, NT >= 1024 ? 4 : WV) void k_run(const DevSys* _
               auto& oth = pick_ref<!O2>(rv, rv2);
 #pragma unroll
               for (int i = 0; i < SPT; ++i) {
-                if (tid + i * NT < nseg) {
+                if (ts + i * NT < nseg) {
                   SegWalk<R> wo(anchor<DIM, R>(to, an[i], nm), uo), wn(anchor<DIM, R>(tn, an[i], nm), un);
                   float segE = 0.f, segX = 0.f;
 #pragma unroll
@@ -351,7 +417,10 @@ __global__ __launch_bounds__(NT, NT >= 1024 ? 4 : WV) void k_run(const DevSys* _
                       wn.step(j);
                     }
                   }
-                  if (MIXED) {
+                  if (FLUSH) {
+                    accE64 += double(segE);
+                    accX64 += double(segX);
+                  } else if (MIXED) {
                     accE32.add(segE);
                     accX32.add(segX);
                   }
@@ -363,9 +432,12 @@ __global__ __launch_bounds__(NT, NT >= 1024 ? 4 : WV) void k_run(const DevSys* _
             else
               lay_loop(std::false_type{});
           } else {
+          // one copy of the loop per decision (uniform): an accepted move also
+          // updates rho += q d (a branch per entry would become per-lane selects)
+          auto entries = [&](auto upd) {
 #pragma unroll
           for (int i = 0; i < SPT; ++i) {
-            if (tid + i * NT < nseg) {
+            if (ts + i * NT < nseg) {
               SegWalk<R> wo(anchor<DIM, R>(to, an[i], nm), uo), wn(anchor<DIM, R>(tn, an[i], nm), un);
               float segE = 0.f, segJ = 0.f;
               R sT = R(0), sT2 = R(0), sL = R(0);  // DER: sums of a Im z, j a Im z, a |G|^2 Re z
@@ -393,21 +465,23 @@ __global__ __launch_bounds__(NT, NT >= 1024 ? 4 : WV) void k_run(const DevSys* _
                   sT2 = fma(R(j), ti, sT2);
                   sL = fma(R(ag2), re, sL);
                 }
-                // rho += q d on an accepted move: the charge times the uniform
-                // decision (0 when rejected, which adds an exact zero) instead
-                // of a branch the compiler would turn into per-lane selects
-                rv[i][j].x += double(qa * dx);
-                rv[i][j].y += double(qa * dy);
+                if (decltype(upd)::value) {
+                  rv[i][j].x += double(q * dx);
+                  rv[i][j].y += double(q * dy);
+                }
                 if (j + 1 < SEG) {
                   wo.step(j);
                   wn.step(j);
                 }
               }
-              if (MIXED) {
+              if (FLUSH) {
+                accE64 += double(segE);
+                if (JAS) accJ64 += double(segJ);
+              } else if (MIXED) {
                 accE32.add(segE);
                 if (JAS) accJ32.add(segJ);
               }
-              if (DER) {
+              if constexpr (DER) {
 #pragma unroll
                 for (int d = 0; d < DIM; ++d) dv[d] = fma(double(sT), double(unpack_n(an[i], d)), dv[d]);
                 dv[DIM - 1] += double(sT2);
@@ -415,23 +489,28 @@ __global__ __launch_bounds__(NT, NT >= 1024 ? 4 : WV) void k_run(const DevSys* _
               }
             }
           }
+          };
+          if (acc)
+            entries(std::true_type{});
+          else
+            entries(std::false_type{});
           }
           const double q2 = qk * qk;
-          v0 = q2 * (MIXED ? accE32.value() : accE64);
-          if (LAY) v0 += 2.0 * qk * (MIXED ? accX32.value() : accX64);
-          if (JAS) v1 = q2 * (MIXED ? accJ32.value() : accJ64);
+          v0 = q2 * (MIXED && !FLUSH ? accE32.value() : accE64);
+          if (LAY) v0 += 2.0 * qk * (MIXED && !FLUSH ? accX32.value() : accX64);
+          if (JAS) v1 = q2 * (MIXED && !FLUSH ? accJ32.value() : accJ64);
           if (!UJ)
-            v0 += qk * real_move_own<DIM, MIXED, PD, NT, PPR, ORTHO, XTRA, false, false, LAY>(
+            v0 += qk * real_move_own<DIM, MIXED, PD, NT, PPR, ORTHO, XTRA, false, false, LAY, FLUSH>(
                            xn, xo, k, ps, pq, lpos, lq, n, S, c64, c32, CV ? fk : frame_k(S), nullptr, 0, nullptr,
                            lay, n0, LAY ? S->dz2 : 0.0);
         }
         if (UJ) {  // the u term moves with a neutral particle too
           UOut<DIM> uo;
-          const double er = real_move_own<DIM, MIXED, PD, NT, PPR, ORTHO, XTRA, UJ, DER>(
+          const double er = real_move_own<DIM, MIXED, PD, NT, PPR, ORTHO, XTRA, UJ, DER, false, FLUSH>(
               xn, xo, k, ps, pq, lpos, lq, n, S, c64, c32, CV ? fk : frame_k(S), psp, S->spin[k], &uo);
           v0 += qk * er;
           v1 += uo.d;
-          if (DER) {
+          if constexpr (DER) {
 #pragma unroll
             for (int d = 0; d < DIM; ++d) dv[NDP + d] = uo.g[d];
             dv[NDV - 1] = uo.l;
@@ -447,77 +526,33 @@ __global__ __launch_bounds__(NT, NT >= 1024 ? 4 : WV) void k_run(const DevSys* _
 #pragma unroll
                 for (int d = 0; d < DIM; ++d) ps[c][d] = xn[d];
           }
-          n_acc += 1;
         }
       }
-      v0 = row_sum16(v0);
-      if (JAS) v1 = row_sum16(v1);
-      if (DER)
+      double v[NV];
+      v[0] = v0;
+      if (JAS) v[NE - 1] = v1;
+      if constexpr (DER)
 #pragma unroll
-        for (int d = 0; d < NDV; ++d) dv[d] = row_sum16(dv[d]);
-      if ((lane & 15) == 0) {
-        double* p = st_part + ((mm * NW + wave) * 4 + (lane >> 4)) * 2;
-        p[0] = v0;
-        p[1] = v1;
-        if (DER) {
-          double* p2 = st_part2 + ((mm * NW + wave) * 4 + (lane >> 4)) * NDV;
-#pragma unroll
-          for (int d = 0; d < NDV; ++d) p2[d] = dv[d];
-        }
-      }
+        for (int d = 0; d < NDV; ++d) v[NE + d] = dv[d];
+      row_sums<NV>(v, lane, st_part + ((mm * NW + wave) * 4 + (lane >> 4)) * NV);
     }
-    if (len > 0) counter = st_cnt[len - 1];
     __syncthreads();  // partials and owner position updates complete
-
-    // ---- outputs of the chunk (cross-row sums in a fixed order) ----
-    if (tid < len) {
-      const size_t idx = size_t(m0 + tid) * n_walkers + w;
-      double e = 0.0, j = 0.0;
-      if (st_k[tid] < 0) {
-        e = j = NAN;
-      } else {
-        const double* p = st_part + tid * NW * 8;
-#pragma unroll
-        for (int v = 0; v < NW * 4; ++v) {
-          e += p[2 * v];
-          j += p[2 * v + 1];
-        }
-      }
-      delta[idx] = e;
-      if (djas) djas[idx] = j;
-      if (DER) {
-        const int kq = st_k[tid];
-        double sv[NDV];
-#pragma unroll
-        for (int d = 0; d < NDV; ++d) sv[d] = 0.0;
-        if (kq >= 0) {
-          const double* p2 = st_part2 + tid * NW * 4 * NDV;
-          for (int v = 0; v < NW * 4; ++v)
-#pragma unroll
-            for (int d = 0; d < NDV; ++d) sv[d] += p2[v * NDV + d];
-        }
-        const double qk = kq >= 0 ? lq[kq] : 0.0;
-        double ug[DIM];  // u term gradient in Cartesian axes
-        if (UJ) frame_to_cart<DIM>(sv + NDP, ORTHO ? S->Eo : S->El, ug);
-#pragma unroll
-        for (int e2 = 0; e2 < DIM; ++e2) {
-          double gx = 0.0;
-#pragma unroll
-          for (int d = 0; d < DIM; ++d) gx = fma(sv[d], S->B[d * 3 + e2], gx);
-          jgrad[idx * DIM + e2] = kq < 0 ? NAN : -2.0 * qk * gx + (UJ ? ug[e2] : 0.0);
-        }
-        jlap[idx] = kq < 0 ? NAN : -2.0 * qk * sv[DIM] + 2.0 * qk * qk * S->jlap_c + (UJ ? sv[NDV - 1] : 0.0);
-      }
-    }
-    due = MIXED && K > 0 && counter >= K;  // uniform: rebuild rho in FP64 between chunks
-    __syncthreads();  // staging buffers and tables are reused by the next chunk
+    counter += n_in;
+    n_acc += n_in;
+    // rebuild rho in FP64 between chunks (mixed form) when due
+    more = m0 + len < n_steps && !(MIXED && K > 0 && counter >= K);
+    int* sk_next = sk == st_k ? st_k + CH : st_k;
+    if (wave == NW - 1) put_out(m0, len, sk);
+    if (more && wave == 0) stage(m0 + len, sk_next);
+    __syncthreads();  // the next chunk is staged, and this one's partials are read
+    sk = sk_next;
     m0 += len;
   }
 
-  // write back (n_acc counted by every thread alike)
+  // write back
 #pragma unroll
   for (int i = 0; i < SPT; ++i) {
-    const int s = tid + i * NT;
+    const int s = ts + i * NT;
     if (s < nseg)
 #pragma unroll
       for (int j = 0; j < SEG; ++j) {
@@ -577,7 +612,7 @@ __global__ void k_queue_reset(int* queue) {
 
 
 // LDS layout of the fused kernel for a chunk of ch moves; returns the total bytes.
-template <int DIM, bool MIXED, int NT, int SPT, bool DER, bool UJ = false>
+template <int DIM, bool MIXED, int NT, bool JAS, bool DER, bool UJ>
 size_t run_layout(const LaunchBatch& b, int ch, RunLds& L) {
   using R = typename std::conditional<MIXED, float, double>::type;
   constexpr int NW = NT / 64;
@@ -610,21 +645,18 @@ size_t run_layout(const LaunchBatch& b, int ch, RunLds& L) {
   o = up16(o + size_t(ch) * DIM * 8);
   L.c2q = uint32_t(o);
   o = up16(o + size_t(ch) * 8);
+  L.mq = uint32_t(o);
+  o = up16(o + size_t(ch) * 8);
   L.part = uint32_t(o);
-  o = up16(o + size_t(ch) * NW * 8 * 8);
+  o = up16(o + size_t(ch) * NW * 4 * size_t((JAS ? 2 : 1) + (DER ? (DIM + 1) * (UJ ? 2 : 1) : 0)) * 8);
   L.k = uint32_t(o);
-  o = up16(o + size_t(ch) * 4);
+  o = up16(o + size_t(ch) * 8);
   L.acc = uint32_t(o);
   o = up16(o + size_t(ch) * 4);
-  L.cnt = uint32_t(o);
-  o = up16(o + size_t(ch) * 4);
+  L.info = uint32_t(o);
+  o = up16(o + 8);
   L.next = uint32_t(o);
   o = up16(o + 4);
-  L.part2 = 0;
-  if (DER) {
-    L.part2 = uint32_t(o);
-    o = up16(o + size_t(ch) * NW * 4 * (DIM + 1) * (UJ ? 2 : 1) * 8);
-  }
   L.ch = ch;
   // between chunks everything from ctab on holds per-chunk data only, so the
   // rebuild's tables may fill all of it
@@ -657,10 +689,10 @@ int run_inst(const LaunchBatch& b, const RunArgs& a) {
   const size_t budget = RUN_LDS_BUDGET / size_t(per_cu);
   RunLds L{};
   int ch = b.run_chunk > 0 ? std::min(b.run_chunk, RUN_CHUNK) : RUN_CHUNK;
-  size_t lds = run_layout<DIM, MIXED, NT, SPT, DER, UJ>(b, ch, L);
+  size_t lds = run_layout<DIM, MIXED, NT, (JM > 0), DER, UJ>(b, ch, L);
   if (b.run_chunk <= 0)
-    while (lds > budget && ch > 8) lds = run_layout<DIM, MIXED, NT, SPT, DER, UJ>(b, --ch, L);
-  while (lds > RUN_LDS_BUDGET && ch > 1) lds = run_layout<DIM, MIXED, NT, SPT, DER, UJ>(b, --ch, L);
+    while (lds > budget && ch > 8) lds = run_layout<DIM, MIXED, NT, (JM > 0), DER, UJ>(b, --ch, L);
+  while (lds > RUN_LDS_BUDGET && ch > 1) lds = run_layout<DIM, MIXED, NT, (JM > 0), DER, UJ>(b, --ch, L);
   if (lds > RUN_LDS_BUDGET) return RUN_NO_FIT;
   // queue mode: ceil(W / walkers_per_block) workgroups take walkers from a
   // counter in the state buffer
@@ -685,8 +717,7 @@ int run_inst(const LaunchBatch& b, const RunArgs& a) {
 // Workgroup shapes of the fused kernel (threads NT, segments per thread SPT).
 // A shape is available for a batch when NT SPT covers its largest segment
 // count s and no smaller SPT would (so each NT appears once); `threads`
-// picks among the available ones, 0 = the default (the first listed that is
-// available):
+// picks among the available ones, 0 = the first listed that is available:
 //   s <= 256: 256 x 1          s <= 512: 256 x 2
 //   s <= 1024: 1024 x 1, or 512 x 2      s <= 2048: 512 x 4
 // (1024 x 1 is also available for s <= 512).  Workgroups sized to small
@@ -746,9 +777,9 @@ int run_jp(const LaunchBatch& b, const RunArgs& a) {
   EW_RUN(256, 2, 2);
   EW_RUN_X(1024, 1, 1);
   // 512 x 2 also at four waves per SIMD (two workgroups per CU, 128
-  // registers): faster for the FP32-mixed form, slower for FP64.  The
-  // Jastrow-derivative kernels (JM 2, 4) need more registers: they stay at
-  // two waves whatever the tuning says (the autotuner probes without them).
+  // registers).  The Jastrow-derivative kernels (JM 2, 4) need more registers:
+  // they stay at two waves whatever the tuning says (the autotuner probes
+  // without them).
   constexpr bool DERJ = JM == 2 || JM == 4;
   if (!DERJ && nt == 512 && spt == 2 && ppr == 2 && wv == 4 && !queue)
     return xtra ? run_inst<DIM, MIXED, 512, 2, 2, JM, PD, ORTHO, true, 4, LAY>(b, a)
