@@ -305,8 +305,9 @@ ewald_status ewald_run_moves_grad_batch(ewald_batch *b, void *state, int n_steps
  * tunes gang and vector sizes by hand, Sec. 3.3).  One workgroup serves one walker;
  *   threads        workgroup size, which fixes segments of 4 G per thread and
  *                  particles per thread: 0 = default for the largest segment
- *                  count s of the batch (s <= 512: 256; s <= 1024: 1024;
- *                  s <= 2048: 512); also available: 1024 for s <= 1024
+ *                  count s of the batch (s <= 512: 256; s <= 1024: 1024, or
+ *                  512 where more walkers than compute units fill the
+ *                  device so; s <= 2048: 512); also available: 1024 for s <= 1024
  *                  and 512 for 512 < s <= 1024; other values give E_ARG
  *   chunk          at most this many moves staged per chunk, 1..64 (fewer
  *                  when LDS does not hold them), or 0 = as many as LDS allows
@@ -315,8 +316,9 @@ ewald_status ewald_run_moves_grad_batch(ewald_batch *b, void *state, int n_steps
  *                  cell has an orthogonal-sublattice frame (ewald_sys_geometry);
  *                  applies to ewald_energy_batch as well
  *   waves          waves per SIMD the kernel is compiled for, for workgroups
- *                  of 256 and 512 threads: 0 or 2 = default (256 registers
- *                  per lane, constants in vector registers), 3 or 4 = more
+ *                  of 256 and 512 threads: 0 = chosen by the walkers per CU
+ *                  (2 in the queue mode and at 512 threads), 2 = 256 registers
+ *                  per lane, constants in vector registers, 3 or 4 = more
  *                  workgroups per CU with the constants in scalar registers
  *                  (256 threads: 3 or 4; 512 threads with 2 segments per
  *                  thread: 4); other combinations give E_ARG (1024-thread

@@ -1469,6 +1469,8 @@ ewald_status ewald_batch_set_tuning(ewald_batch* b, int threads, int chunk, int 
   if (waves > 2) {  // the 256-thread kernels come in these variants, and 512 x 2 at four waves
     LaunchBatch L = b->lb;
     L.run_threads = threads;
+    L.run_waves = waves;
+    L.run_wpb = 0;
     RunPlan p{};
     plan_run(L, &p);
     const bool ok = p.threads == 256 || (waves == 4 && p.threads == 512 && p.spt == 2);

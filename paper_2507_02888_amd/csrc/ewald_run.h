@@ -744,17 +744,51 @@ inline int run_shape(int max_n_seg, int max_particles, int threads, int* nt, int
   return 0;
 }
 
+// The shape when nothing is fixed, by how many walkers each CU gets: a kernel
+// bounded to w waves per SIMD holds w workgroups of 256 threads (w / 2 of 512)
+// per CU at once, each then slower than with more registers.
+// 256 threads: one round of walkers takes 1.0 to 1.6 times as long at three
+// waves as at two, 1.4 to 1.6 times at four (250-electron fcc, 300-electron
+// hexagonal, bilayer and 64..512-electron diamond sweeps, both forms).  Two
+// waves against the choice here (ms): fcc 1024 walkers x 256 moves mixed 1.10
+// and 0.81, FP64 0.86 and 0.70; hexagonal 2048 x 512 FP64 2.30 and 1.85, mixed 2.92
+// and 2.02; diamond 4096 x 256 mixed 4.96 and 3.68, FP64 4.08 and 3.28; bilayer
+// 2048 x 512 mixed 3.42 and 2.47.
+// 512 < s <= 1024: two workgroups of 512 threads at four waves take 1.6 to 1.75
+// times the round of one of 1024 (N = 1024, 1024 walkers x 256 moves FP64: 1.94 and
+// 2.23 ms).  The derivative kernels run one workgroup of 512 threads with 256
+// registers per lane whatever the batch (with the u term and 128 moves: 1024
+// walkers 3.0 ms and 8 walkers 0.71; at 1024 threads, which spill, 3.5 and 0.84).  Walkers of more particles than the registers
+// hold, or with ions, keep 1024 threads.
+inline void run_defaults(const LaunchBatch& b, bool der, int* threads, int* waves) {
+  *threads = b.run_threads;
+  *waves = b.run_waves;
+  if (*waves != 0 || b.run_wpb > 0) return;
+  auto rounds = [&](int per_cu) { return (b.n_walkers + per_cu * b.n_cu - 1) / (per_cu * b.n_cu); };
+  int nt = 0, spt = 0, ppr = 0;
+  if (!run_shape(b.max_n_seg, b.max_particles, *threads, &nt, &spt, &ppr)) return;
+  if (nt == 256) {
+    const double t2 = rounds(2), t3 = rounds(3) * 1.25, t4 = rounds(4) * 1.5;
+    *waves = t2 <= t3 && t2 <= t4 ? 2 : t4 <= t3 ? 4 : 3;
+  } else if (nt == 1024 && *threads == 0 && b.max_n_seg > 512 && b.max_particles > 512 && b.max_particles <= 1024 &&
+             b.max_fixed == 0 && (der || rounds(2) * 1.75 < rounds(1))) {
+    *threads = 512;
+    *waves = der ? 2 : 4;
+  }
+}
+
 template <int DIM, bool MIXED, int JM, int PD, bool ORTHO, bool LAY = false>
 int run_jp(const LaunchBatch& b, const RunArgs& a) {
   static_assert(RUN_CHUNK <= 256, "staging uses one thread per move");
-  int nt = 0, spt = 0, ppr = 0;
-  if (!run_shape(b.max_n_seg, b.max_particles, b.run_threads, &nt, &spt, &ppr)) return RUN_NO_FIT;
+  int nt = 0, spt = 0, ppr = 0, threads = 0, waves = 0;
+  run_defaults(b, JM == 2 || JM == 4, &threads, &waves);
+  if (!run_shape(b.max_n_seg, b.max_particles, threads, &nt, &spt, &ppr)) return RUN_NO_FIT;
   // XTRA: particles beyond the registers' share, or fixed ions, in some
   // walker.  Leaving those loops out pays at 512 and 1024 threads; the
   // 256-thread kernels keep them (without them the compiler spends more
   // registers there and runs slower).
   const bool xtra = b.max_particles > ppr * nt || b.max_fixed > 0;
-  const int wv = b.run_waves > 0 ? b.run_waves : 2;
+  const int wv = waves > 0 ? waves : 2;
   // the queue mode is compiled for two waves per SIMD; the host rejects it
   // with other wave counts
   const bool queue = b.run_wpb > 0;

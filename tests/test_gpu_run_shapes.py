@@ -1,10 +1,16 @@
-"""The fused sweep's staging of chunks against the per-step calls, on sequences
-that move few particles again and again, with chunks of 1, 2, 63 and 64 moves.
+"""The fused sweep's launch shapes when nothing is fixed (chosen by the walkers
+per compute unit) against the shapes fixed by hand, at the walker counts where
+the choice changes; and the staging of chunks against the per-step calls, on
+sequences that move few particles again and again, with chunks of 1, 2, 63 and
+64 moves.
 
-Tolerances, from before any run: FP64 sums in another order agree to 1e-12 of the
-total energy or the largest change of it per move (at most 1024 particles and 990
-segments of 8 terms: 10^4 roundings of 1.1e-16).  Mixed form: FP32 partial sums
-over other groups, 1e-6 Ha and 3e-6 on Jastrow deltas.
+Tolerances, from before any run: shapes that differ in the waves per SIMD only,
+or in the order of FP64 sums, agree to rounding: N_terms roundings of terms that
+are below the total energy or the largest change of it, 1e-12 of it (at most 1024 particles and 990 segments
+of 8 terms: 10^4 roundings of 1.1e-16).  512 x 2 and 1024 x 1 in the mixed form
+add the same FP32 segment sums and the same FP32 pair terms up in FP64, so the same bound
+holds.  The fused sweep against the per-step calls in the mixed form: FP32
+partial sums over other groups, 1e-6 Ha and 3e-6 on Jastrow deltas.
 """
 import numpy as np
 import pytest
@@ -23,6 +29,10 @@ def need_gpu():
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
     ew.load()
+
+
+def cus():
+    return torch.cuda.get_device_properties(0).multi_processor_count
 
 
 class Sweep:
@@ -75,6 +85,48 @@ def check(a, b, tols, what):
         d = float(np.max(np.abs(np.nan_to_num(x - y))))
         print(f"  {what} output {i}: {d:.3e} (allowed {tols[i]:.1e})", flush=True)
         assert d <= tols[i], (what, i, d)
+
+
+@pytest.mark.parametrize("precision", [FP64, MIXED], ids=["fp64", "mixed"])
+@pytest.mark.parametrize("rounds,more,waves", [(0, 1, 2), (2, 0, 2), (2, 1, 3), (3, 1, 4), (4, 1, 3)])
+def test_small_walkers_default_waves(precision, rounds, more, waves):
+    W = rounds * cus() + more
+    s = Sweep(2, W, 6, precision)
+    got = s.result()
+    t = s.batch.tuning()
+    print(f"[waves] W={W} {t}", flush=True)
+    assert t["threads"] == 256 and t["waves"] == waves
+    s.batch.set_tuning(threads=256, waves=2)
+    tol = 1e-12 * s.scale
+    check(got, s.result(), [tol, tol, 1e-9, 1e-9], "two waves")
+
+
+@pytest.mark.parametrize("precision", [FP64, MIXED], ids=["fp64", "mixed"])
+@pytest.mark.parametrize("rounds,more,threads", [(1, 0, 1024), (1, 1, 512), (2, 0, 512), (2, 1, 1024)])
+def test_large_walkers_default_threads(precision, rounds, more, threads):
+    W = rounds * cus() + more
+    s = Sweep(5, W, 5, precision)
+    got = s.result()
+    t = s.batch.tuning()
+    print(f"[threads] W={W} {t}", flush=True)
+    assert t["threads"] == threads and t["waves"] == (4 if threads == 512 else 0)
+    s.batch.set_tuning(threads=1024)
+    tol = 1e-12 * s.scale
+    check(got, s.result(), [tol, tol, 1e-9, 1e-9], "1024 threads")
+
+
+@pytest.mark.parametrize("precision", [FP64, MIXED], ids=["fp64", "mixed"])
+@pytest.mark.parametrize("u_term", [False, True], ids=["p", "pu"])
+def test_derivative_sweep_default(precision, u_term):
+    s = Sweep(5, 3, 9, precision, u_term=u_term)
+    got = s.result(der=True)
+    s.batch.set_tuning(threads=1024)
+    ref = s.result(der=True)
+    tol = 1e-12 * s.scale
+    # derivative sums stay FP32 within a segment in both shapes
+    print(f"[derivatives] {u_term}", flush=True)
+    check(got, ref, [tol, tol, 1e-11 * max(1.0, float(np.nanmax(np.abs(ref[2])))),
+                     1e-11 * max(1.0, float(np.nanmax(np.abs(ref[3])))), 1e-9, 1e-9], "1024 threads")
 
 
 @pytest.mark.parametrize("precision", [FP64, MIXED], ids=["fp64", "mixed"])
