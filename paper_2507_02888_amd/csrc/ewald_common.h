@@ -41,14 +41,17 @@ __device__ __forceinline__ double wrap01(double x) {
 
 // Cartesian row vector -> wrapped fractional coordinates.
 template <int DIM>
+__device__ __forceinline__ double to_frac1(const double* r, const double* Ainv, int d) {
+  double v = 0.0;
+#pragma unroll
+  for (int e = 0; e < DIM; ++e) v = fma(r[e], Ainv[e * 3 + d], v);
+  return wrap01(v);
+}
+
+template <int DIM>
 __device__ __forceinline__ void to_frac(const double* r, const double* Ainv, double* s) {
 #pragma unroll
-  for (int d = 0; d < DIM; ++d) {
-    double v = 0.0;
-#pragma unroll
-    for (int e = 0; e < DIM; ++e) v = fma(r[e], Ainv[e * 3 + d], v);
-    s[d] = wrap01(v);
-  }
+  for (int d = 0; d < DIM; ++d) s[d] = to_frac1<DIM>(r, Ainv, d);
 }
 
 // exp(2 pi i x) in turns: reduce x to the nearest quarter turn q and a
@@ -955,13 +958,18 @@ struct SegWalk {
 // Waves: NW per workgroup, gw of them (a power of two) share the pieces'
 // groups, NS groups per wave and pass (the longest with the shortest, the
 // groups being sorted by length), and NW / gw of them share the particles.
-// Their sums meet in `rc` (LDS, 1 KB per segment of the groups' longest pieces;
-// the tables' own may serve, such a pass being the only one), in a fixed order.
+// Their sums meet in `rc` (LDS, rc_bytes of it, 1 KB per segment of the groups'
+// longest pieces at the least; the tables' own may serve, such a pass being the only
+// one), in a fixed order: where every share's sums fit, all waves then take a
+// part of the entries, else one share after the other adds its own.  (Small systems
+// wait for this end, not for arithmetic: a bilayer of 40 electrons, 30 walkers, takes
+// 17.5 us per energy call so, 29.0 one share after the other, its loads in
+// between.)
 // Each pass takes the particles `tile` at a time (a multiple of four) through LDS
-// phase tables at `tabs` (S->ph_stride bytes per particle).  `sink(idx, v,
-// pos)` receives each entry once: slot idx, the sum v without the fixed
-// ions, pos the entry's place in grp_w.  All threads must call it; the last
-// thing it does before the sinks is a barrier.
+// phase tables at `tabs` (S->ph_stride bytes per particle), from the fractional
+// coordinates frac(p, d).  `sink(idx, v, w)`
+// receives each entry once: slot idx, the sum v without the fixed ions, w its
+// weights from grp_w (WGT; else unused).  All threads must call it.
 typedef double f64x2 __attribute__((ext_vector_type(2)));
 
 __device__ __forceinline__ cplx<double> lds_entry(const char* p) {
@@ -988,8 +996,8 @@ __device__ __forceinline__ void fill_run(char* row, double s, double off, int m0
 // four, empty ones, all zero): per particle the rows exp(i n th_d), n = 0 .. nmax[d], of
 // the leading dimensions (the first carries the charge) and
 // exp(i (h + 1/2) th_last), h = 0 .. ph_hn - 1.
-template <int DIM, int NT>
-__device__ __forceinline__ void fill_tables(const DevSys* __restrict__ S, const double* pos, const double* q, int p0,
+template <int DIM, int NT, typename Pos>
+__device__ __forceinline__ void fill_tables(const DevSys* __restrict__ S, const Pos& frac, const double* q, int p0,
                                             int np, int turn_at, char* tabs) {
   const int runs = S->ph_runs;  // of the longest row
   const int stride = S->ph_stride;
@@ -1004,7 +1012,7 @@ __device__ __forceinline__ void fill_tables(const DevSys* __restrict__ S, const 
     if (m0 >= m1) continue;
     char* t = tabs + pp * stride + off;
     if (pp < np)
-      fill_run(t, pos[(p0 + pp) * DIM + d], last ? 0.5 : 0.0, m0, m1, d == 0 ? q[p0 + pp] : 1.0);
+      fill_run(t, frac(p0 + pp, d), last ? 0.5 : 0.0, m0, m1, d == 0 ? q[p0 + pp] : 1.0);
     else
       for (int m = m0; m < min(m0 + 8, m1); ++m) *reinterpret_cast<f64x2*>(t + 16 * m) = f64x2{0.0, 0.0};
   }
@@ -1014,10 +1022,10 @@ __device__ __forceinline__ double flip_sign(double v, uint32_t mask) {
   return __hiloint2double(__double2hiint(v) ^ int(mask), __double2loint(v));
 }
 
-template <int DIM, int NW, int NS, typename Sink>
-__device__ __forceinline__ void rho_build(const DevSys* __restrict__ S, const double* pos, const double* q, int n,
-                                          char* tabs, int tile, cplx<double>* rc, int gw, int g_lo, int g_hi,
-                                          Sink&& sink) {
+template <int DIM, int NW, int NS, bool WGT, typename Pos, typename Sink>
+__device__ __forceinline__ void rho_build(const DevSys* __restrict__ S, const Pos& frac, const double* q, int n,
+                                          char* tabs, int tile, cplx<double>* rc, int rc_bytes, int gw, int g_lo,
+                                          int g_hi, Sink&& sink) {
   static_assert(NS == 1 || NS == 2, "groups per wave and pass");
   static_assert(GRP_QMAX == 6, "the block columns' reads are written out");
   constexpr int NT = NW * 64;
@@ -1025,6 +1033,9 @@ __device__ __forceinline__ void rho_build(const DevSys* __restrict__ S, const do
   const int nks = NW / gw, wg = wave & (gw - 1), ks = wave / gw;
   const int stride = S->ph_stride, ou = S->ph_ou;
   char* const tabs1 = tabs + tile * stride;  // the tables of one tile are filled while the other's are read
+  const double2* gwt = reinterpret_cast<const double2*>(S->grp_w);
+  const int at0 = 64 * S->grp_off[g_lo], cnt = 64 * (g_hi < S->n_grp ? S->grp_off[g_hi] : S->n_ent) - at0;
+  const bool slabs = nks > 1 && nks * cnt * int(sizeof(cplx<double>)) <= rc_bytes;  // uniform
   for (int gp = g_lo; gp < g_hi; gp += NS * gw) {
     int grp[NS], Q[NS], o0[NS], o1[NS], oc[NS];
     uint32_t s1[NS], sc[NS];
@@ -1033,7 +1044,7 @@ __device__ __forceinline__ void rho_build(const DevSys* __restrict__ S, const do
     for (int t = 0; t < NS; ++t) {
       const int g = gp + (t == 0 ? wg : 2 * gw - 1 - wg);
       grp[t] = g < g_hi ? g : g_lo;
-      Q[t] = uniform_i(g < g_hi ? S->grp_q[grp[t]] : 0);
+      Q[t] = g < g_hi ? S->grp_q[grp[t]] : 0;
       const uint32_t pk = S->grp_col[grp[t] * 16 + (lane & 15)];
       o0[t] = 16 * int(pk & 0xff);
       o1[t] = S->ph_o1 + 16 * int((pk >> 8) & 0xff);
@@ -1043,11 +1054,13 @@ __device__ __forceinline__ void rho_build(const DevSys* __restrict__ S, const do
 #pragma unroll
       for (int i = 0; i < GRP_QMAX; ++i) ax[t][i] = ay[t][i] = 0.0;
     }
-    fill_tables<DIM, NT>(S, pos, q, 0, min(tile, n), 0, tabs);
+    fill_tables<DIM, NT>(S, frac, q, 0, min(tile, n), 0, tabs);
+#pragma unroll
+    for (int t = 0; t < NS; ++t) Q[t] = uniform_i(Q[t]);
     __syncthreads();
     for (int p0 = 0, b = 0; p0 < n; p0 += tile, b ^= 1) {
       const int left = n - p0;
-      if (left > tile) fill_tables<DIM, NT>(S, pos, q, p0 + tile, min(tile, left - tile), p0 + tile, b ? tabs : tabs1);
+      if (left > tile) fill_tables<DIM, NT>(S, frac, q, p0 + tile, min(tile, left - tile), p0 + tile, b ? tabs : tabs1);
       const int np_pad = (min(tile, left) + 3) & ~3;
       // uniform branches on the groups' lengths (Q[1] <= Q[0]: they are
       // sorted); written as a switch, or as loops for every pair of lengths,
@@ -1094,32 +1107,76 @@ __device__ __forceinline__ void rho_build(const DevSys* __restrict__ S, const do
       __syncthreads();
     }
     const bool odd = lane & 1;
-    for (int k2 = 0; k2 < nks; ++k2) {  // uniform: the particle shares in a fixed order
-      if (k2 == ks) {
+    auto entry = [&](int t, int i) {  // this lane's entry of block column i
+      const double x = ax[t][i], y = ay[t][i];
+      const double nx = dpp_all<0xB1>(x), ny = dpp_all<0xB1>(y);  // the neighbour's (quad_perm [1,0,3,2])
+      return cplx<double>{odd ? nx + y : x - ny, odd ? ny - x : y + nx};
+    };
+    if (slabs) {  // uniform
 #pragma unroll
-        for (int t = 0; t < NS; ++t)
+      for (int t = 0; t < NS; ++t)
 #pragma unroll
-          for (int i = 0; i < GRP_QMAX; ++i)
-            if (i < Q[t]) {
-              const double x = ax[t][i], y = ay[t][i];
-              const double nx = dpp_all<0xB1>(x), ny = dpp_all<0xB1>(y);  // the neighbour's (quad_perm [1,0,3,2])
-              cplx<double> v = {odd ? nx + y : x - ny, odd ? ny - x : y + nx};
-              const int at = (S->grp_off[grp[t]] + i) * 64 + lane;
-              const int idx = S->grp_slot[at];
-              if (idx >= 0) {
-                const int at_rc = at - S->grp_off[g_lo] * 64;
-                if (k2 > 0) {
-                  v.x += rc[at_rc].x;
-                  v.y += rc[at_rc].y;
-                }
-                if (k2 + 1 < nks)
-                  rc[at_rc] = v;
-                else
-                  sink(idx, v, at);
-              }
-            }
+        for (int i = 0; i < GRP_QMAX; ++i)
+          if (i < Q[t]) rc[ks * cnt + (S->grp_off[grp[t]] + i) * 64 - at0 + lane] = entry(t, i);
+      __syncthreads();
+      // a thread's entries two at a time (loads may not pass the sinks' stores;
+      // asking for them before the first tile took registers and was slower)
+      for (int e0 = threadIdx.x; e0 < cnt; e0 += 2 * NT) {
+        int idx[2];
+        double2 w[2];
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+          const int e = e0 + c * NT;
+          idx[c] = e < cnt ? S->grp_slot[at0 + e] : -1;
+          if (WGT) w[c] = e < cnt ? gwt[at0 + e] : double2{0.0, 0.0};
+        }
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+          if (idx[c] < 0) continue;
+          cplx<double> v = rc[e0 + c * NT];
+          for (int k2 = 1; k2 < nks; ++k2) {  // uniform
+            const cplx<double> o = rc[k2 * cnt + e0 + c * NT];
+            v.x += o.x;
+            v.y += o.y;
+          }
+          sink(idx[c], v, w[c]);
+        }
       }
-      if (nks > 1) __syncthreads();
+      __syncthreads();
+    } else {
+      for (int k2 = 0; k2 < nks; ++k2) {  // uniform: the particle shares in a fixed order
+        if (k2 == ks) {
+#pragma unroll
+          for (int t = 0; t < NS; ++t) {
+            const int at = 64 * S->grp_off[grp[t]] + lane;
+            if (k2 + 1 < nks) {
+#pragma unroll
+              for (int i = 0; i < GRP_QMAX; ++i)
+                if (i < Q[t]) {
+                  cplx<double> v = entry(t, i);
+                  cplx<double>* r = rc + at - at0 + 64 * i;
+                  *r = k2 > 0 ? cplx<double>{v.x + r->x, v.y + r->y} : v;
+                }
+            } else {
+              int idx[GRP_QMAX];
+#pragma unroll
+              for (int i = 0; i < GRP_QMAX; ++i) idx[i] = i < Q[t] ? S->grp_slot[at + 64 * i] : -1;
+#pragma unroll
+              for (int i = 0; i < GRP_QMAX; ++i)
+                if (i < Q[t]) {
+                  cplx<double> v = entry(t, i);
+                  if (k2 > 0) {
+                    const cplx<double> r = rc[at - at0 + 64 * i];
+                    v.x += r.x;
+                    v.y += r.y;
+                  }
+                  if (idx[i] >= 0) sink(idx[i], v, WGT ? gwt[at + 64 * i] : double2{0.0, 0.0});
+                }
+            }
+          }
+        }
+        if (nks > 1) __syncthreads();
+      }
     }
   }
 }
@@ -1158,14 +1215,18 @@ inline size_t up16(size_t x) { return (x + 15) & ~size_t(15); }
 constexpr size_t RUN_LDS_BUDGET = 160 * 1024;  // LDS per workgroup on gfx950
 constexpr int RUN_NO_FIT = -1;                 // the fused kernel's LDS does not fit: use the per-step kernels
 
-// Particles per phase-table tile of rho_build with its two tiles within `bytes` of LDS: a multiple
-// of four (a matrix instruction takes four particles), at least four, no more
-// than the largest walker needs.
+// Particles per phase-table tile of rho_build with its tiles within `bytes` of
+// LDS: a multiple of four (a matrix instruction takes four particles), at least
+// four.  One tile where it holds the largest walker of up to 2 TILE_MAX particles,
+// else two of up to TILE_MAX each.
 inline int rho_tile(const LaunchBatch& b, size_t bytes) {
-  const int most = std::min(TILE_MAX, (b.max_particles + 3) & ~3);
-  return std::max(4, std::min(most, int(bytes / (2 * size_t(b.max_ph))) & ~3));
+  const int most = (b.max_particles + 3) & ~3;
+  if (most <= 2 * TILE_MAX && size_t(most) * size_t(b.max_ph) <= bytes) return most;
+  return std::max(4, std::min(std::min(TILE_MAX, most), int(bytes / (2 * size_t(b.max_ph))) & ~3));
 }
-inline size_t rho_lds(const LaunchBatch& b, int tile) { return 2 * size_t(tile) * size_t(b.max_ph); }
+inline size_t rho_lds(const LaunchBatch& b, int tile) {
+  return (b.max_particles <= tile ? 1 : 2) * size_t(tile) * size_t(b.max_ph);
+}
 
 // Workgroups of this kernel that fit on one CU by registers (4 SIMDs, 512
 // VGPRs per lane each); the fused kernel sizes its LDS so as not to lower it.

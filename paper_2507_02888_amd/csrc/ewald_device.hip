@@ -40,13 +40,18 @@ namespace ewald {
 // stored in the walker state.
 // UJ: the Jastrow value also takes the two-body polynomial term u over the
 // mobile pairs (Sec. 2.3, Eq. (8)).
+// Registers: four waves per SIMD (128 per lane) hold the loops without the u term;
+// with it, or with the degree-32 polynomial in the orthogonal frame, 60 to 120 of
+// them were spilled inside the pair loop, and three waves (168) are faster at
+// any batch (ms, N = 1024, 1024 walkers, with u: 2.6 and 2.35; degree 32: 2.67 and 1.52;
+// 256 walkers with u 1.19 and 0.87).
 constexpr int RED_ENERGY = 48;  // LDS doubles for k_energy's reduction
 template <int DIM, int PD, bool ORTHO, bool UJ>
-__global__ __launch_bounds__(BLOCK, 4) void k_energy(const DevSys* __restrict__ systems,
+__global__ __launch_bounds__(BLOCK, UJ || (PD > 16 && ORTHO) ? 3 : 4) void k_energy(const DevSys* __restrict__ systems,
                                                   const DevWalker* __restrict__ walkers,
                                                   const double* __restrict__ pos, char* __restrict__ state,
                                                   double* __restrict__ energy, double* __restrict__ jastrow,
-                                                  int lds_pos, int tile) {
+                                                  int lds_pos, int tile, int rc_bytes) {
   extern __shared__ double smem[];
   const DevWalker W = walkers[blockIdx.x];
   const int w = W.id, tid = threadIdx.x;
@@ -81,7 +86,6 @@ __global__ __launch_bounds__(BLOCK, 4) void k_energy(const DevSys* __restrict__ 
     hdr->pending_s[0] = hdr->pending_s[1] = hdr->pending_s[2] = 0.0;
     hdr->drift_max = 0.0;
   }
-  __syncthreads();
 
   // reciprocal space: every entry of rho goes to the state as it is formed, with
   // its terms of the energy and the Jastrow value
@@ -93,15 +97,16 @@ __global__ __launch_bounds__(BLOCK, 4) void k_energy(const DevSys* __restrict__ 
   const int gw = rho_waves(S->n_grp, 2, BLOCK / 64);
   cplx<double>* rc = reinterpret_cast<cplx<double>*>(tabs);  // waves sharing the particles: one pass, after the tables' last use
   double2* rho2 = reinterpret_cast<double2*>(rho);
-  const double2* gwt = reinterpret_cast<const double2*>(S->grp_w);
   double er = 0.0, ej = 0.0;
-  rho_build<DIM, BLOCK / 64, 2>(S, spos, S->mobile_q, n0, tabs, tile, rc, gw, 0, S->n_grp,
-                                [&](int idx, cplx<double> v, int at) {
+  // the tables are built from the arguments, not from spos: one trip to memory
+  // before the first tile instead of three in a row
+  auto frac = [&](int p, int d) { return to_frac1<DIM>(pw + p * DIM, S->Ainv, d); };
+  rho_build<DIM, BLOCK / 64, 2, true>(S, frac, S->mobile_q, n0, tabs, tile, rc, rc_bytes, gw, 0, S->n_grp,
+                                [&](int idx, cplx<double> v, double2 w2) {
                                   if (nfix > 0) {
                                     v.x += S->rho_fix[2 * idx];
                                     v.y += S->rho_fix[2 * idx + 1];
                                   }
-                                  const double2 w2 = gwt[at];
                                   const double m2 = v.x * v.x + v.y * v.y;
                                   er = fma(w2.x, m2, er);
                                   ej = fma(w2.y, m2, ej);
@@ -110,15 +115,15 @@ __global__ __launch_bounds__(BLOCK, 4) void k_energy(const DevSys* __restrict__ 
   if (lay) {
     __syncthreads();
     double2* rho12 = rho2 + size_t(SEG) * nseg;
-    rho_build<DIM, BLOCK / 64, 2>(S, spos + size_t(n0) * DIM, S->mobile_q + n0, n - n0, tabs, tile, rc, gw, 0,
-                                  S->n_grp, [&](int idx, cplx<double> v, int at) {
+    rho_build<DIM, BLOCK / 64, 2, true>(S, [&](int p, int d) { return frac(n0 + p, d); }, S->mobile_q + n0, n - n0,
+                                  tabs, tile, rc, rc_bytes, gw, 0, S->n_grp, [&](int idx, cplx<double> v, double2 w2) {
                                     if (nfix > 0) {
                                       v.x += S->rho_fix1[2 * idx];
                                       v.y += S->rho_fix1[2 * idx + 1];
                                     }
                                     const double2 v0 = rho2[idx];  // written by this thread
                                     const double m2 = v.x * v.x + v.y * v.y;
-                                    er = fma(gwt[at].x, m2, er);
+                                    er = fma(w2.x, m2, er);
                                     er = fma(2.0 * S->wx[idx], v0.x * v.x + v0.y * v.y, er);
                                     rho12[idx] = {v.x, v.y};
                                   });
@@ -137,7 +142,6 @@ __global__ __launch_bounds__(BLOCK, 4) void k_energy(const DevSys* __restrict__ 
     for (int d = 0; d < DIM; ++d) lpos[d * lds_pos + i] = x[d];
     lq[i] = S->mobile_q[i];
   }
-  __syncthreads();
   // the pair loop's constants in vector registers (see frame_k_vector)
   const FrameK K = frame_k_vector(S);
   double cf64[PD + 1];
@@ -147,58 +151,61 @@ __global__ __launch_bounds__(BLOCK, 4) void k_energy(const DevSys* __restrict__ 
 #pragma unroll
     for (int i = 0; i <= PD; ++i) cf64[i] = S->p64[i + z];
   }
+  __syncthreads();
   PairAcc<false, PD> pr(cf64, S->p32, K);
   const double rc2 = S->rc2;
-  const int half = (n - 1) / 2;
+  const int half = (n - 1) / 2, full = half & ~3;  // partners in whole groups of four
+  // A particle's partners in shares, an item (a particle's share) per thread and
+  // round: with a thread per particle, 54 particles leave four fifths of the
+  // threads idle and 300 take two rounds, the second with 44.  (Energy calls, us:
+  // 54 particles, one walker 19.3 and 17.0; 100 particles, 30 walkers 26.8 and
+  // 23.4; 300 particles, 20 walkers 133 and 102.)
+  const int parts = S->pair_parts, per_f = S->pair_full, per_m = S->pair_more;
   double eu = 0.0;  // UJ: this thread's share of sum_{i<j} u(r_ij)
-  for (int i = tid; i < n; i += BLOCK) {
+  for (int item = tid; item < n * parts; item += BLOCK) {
+    const int share = item / n, i = item - share * n;
     double si[DIM];
 #pragma unroll
     for (int d = 0; d < DIM; ++d) si[d] = lpos[d * lds_pos + i];
     const double qi = lq[i];
     const int spi = UJ ? S->spin[i] : 0;
     const int li = i >= n0 ? 1 : 0;  // plane of particle i (layered systems)
-    // the partners i + 1 .. i + half (cyclically), which every particle has:
-    // the group bounds are the same for every lane and no partner is an ion
-    for (int m0 = 0; m0 < half; m0 += 4) {
+    // the partners i + 1 .. i + full (cyclically), which every particle has
+    const int f_end = min((share + 1) * per_f, full);
+    for (int m0 = share * per_f; m0 < f_end; m0 += 4) {
       double qq[4], r2[4], ir[4];
       bool uneq[4];
 #pragma unroll
       for (int c = 0; c < 4; ++c) {
         int j = i + m0 + c + 1;
         if (j >= n) j -= n;
-        if (m0 + c < half) {
-          double sj[DIM];
+        double sj[DIM];
 #pragma unroll
-          for (int d = 0; d < DIM; ++d) sj[d] = lpos[d * lds_pos + j];
-          qq[c] = qi * lq[j];
-          r2[c] = image_r2<DIM, ORTHO>(si, sj, S, n_cand, K);
-          if (lay) r2[c] += ((j >= n0 ? 1 : 0) != li) ? S->dz2 : 0.0;
-          uneq[c] = UJ && S->spin[j] != spi;
-        } else {
-          qq[c] = 0.0;
-          r2[c] = rc2;
-          uneq[c] = false;
-        }
+        for (int d = 0; d < DIM; ++d) sj[d] = lpos[d * lds_pos + j];
+        qq[c] = qi * lq[j];
+        r2[c] = image_r2<DIM, ORTHO>(si, sj, S, n_cand, K);
+        if (lay) r2[c] += ((j >= n0 ? 1 : 0) != li) ? S->dz2 : 0.0;
+        uneq[c] = UJ && S->spin[j] != spi;
       }
 #pragma unroll
       for (int c = 0; c < 4; ++c) ir[c] = rsqrt_pos(r2[c]);
       pr.template add_ir<4>(qq, r2, ir);
       if (UJ)
 #pragma unroll
-        for (int c = 0; c < 4; ++c) eu += u_pair(S, m0 + c < half, uneq[c], r2[c], ir[c]);
+        for (int c = 0; c < 4; ++c) eu += u_pair(S, true, uneq[c], r2[c], ir[c]);
     }
-    // then i + n/2 for i < n/2 when n is even, and every fixed ion
-    const int n_mob = ((n & 1) == 0 && i < n / 2) ? 1 : 0;
+    // then up to i + half, i + n/2 for i < n/2 when n is even, and every fixed ion
+    const int n_mob = half - full + (((n & 1) == 0 && i < n / 2) ? 1 : 0);
     const int n_part = n_mob + nfix;
-    for (int m0 = 0; m0 < n_part; m0 += 4) {
+    const int m_end = min((share + 1) * per_m, n_part);
+    for (int m0 = share * per_m; m0 < m_end; m0 += 4) {
       double qq[4], r2[4], ir[4];
       bool mobc[4], uneq[4];
 #pragma unroll
       for (int c = 0; c < 4; ++c) {
         const int m = m0 + c;
         const bool mob = m < n_mob, fix = !mob && m < n_part;
-        int j = i + half + m + 1;
+        int j = i + full + m + 1;
         if (j >= n) j -= n;
         double sj[DIM];
         if (mob) {
@@ -643,7 +650,8 @@ constexpr int REBUILD_GROUPS = 4;
 template <int DIM>
 __global__ __launch_bounds__(REBUILD_NT) void k_rebuild(const DevSys* __restrict__ systems,
                                                         const DevWalker* __restrict__ walkers,
-                                                        char* __restrict__ state, int tile, int n_walkers, int per) {
+                                                        char* __restrict__ state, int tile, int rc_bytes, int n_walkers,
+                                                        int per) {
   extern __shared__ double smem[];
   const int g_lo = blockIdx.y * REBUILD_GROUPS;
   // lane i looks at walker i of the workgroup's share (every wave alike)
@@ -674,9 +682,9 @@ __global__ __launch_bounds__(REBUILD_NT) void k_rebuild(const DevSys* __restrict
     double2* rl = reinterpret_cast<double2*>(rho) + size_t(SEG) * nseg * l;
     const double* rfix = S->n_fixed > 0 ? (l == 0 ? S->rho_fix : S->rho_fix1) : nullptr;
     // the waves' shares meet in the tables' LDS (one pass, after their last use)
-    rho_build<DIM, REBUILD_NT / 64, 1>(S, spos + size_t(p0) * DIM, S->mobile_q + p0, p1 - p0, tabs, tile,
-                                       reinterpret_cast<cplx<double>*>(smem), gw, g_lo, g_hi,
-                                       [&](int idx, cplx<double> v, int) {
+    rho_build<DIM, REBUILD_NT / 64, 1, false>(S, [&](int p, int d) { return spos[(p0 + p) * DIM + d]; },
+                                       S->mobile_q + p0, p1 - p0, tabs, tile, reinterpret_cast<cplx<double>*>(smem), rc_bytes, gw, g_lo, g_hi,
+                                       [&](int idx, cplx<double> v, double2) {
                                          if (rfix) {
                                            v.x += rfix[2 * idx];
                                            v.y += rfix[2 * idx + 1];
@@ -708,16 +716,17 @@ int energy_inst(const LaunchBatch& b, const double* pos, char* state, double* en
   auto* kern = k_energy<DIM, PD, ORTHO, UJ>;
   // phase-table tiles (sharing their LDS with the pair loop's positions) as
   // large as LDS allows without lowering the workgroups per CU that
-  // registers allow (four: the kernel is bounded to four waves per SIMD)
+  // registers allow (three or four)
   static const int per_cu = blocks_per_cu(kern, BLOCK);
-  const size_t budget = RUN_LDS_BUDGET / size_t(per_cu);
+  const size_t budget = RUN_LDS_BUDGET / size_t(per_cu) & ~size_t(2047);  // (LDS is given out in blocks)
   const int tile = rho_tile(b, budget - head);
   // waves that share the particles (few groups) add up their sums in the tables' place
-  const size_t share = rho_waves(b.min_grp, 2, BLOCK / 64) < BLOCK / 64 ? size_t(BLOCK / 64) * GRP_BYTES : 0;
+  const size_t share = rho_waves(b.min_grp, 2, BLOCK / 64) < BLOCK / 64 ? budget - head : 0;
+  static_assert(size_t(BLOCK / 64) * GRP_BYTES + RED_ENERGY * 8 <= RUN_LDS_BUDGET / 4, "shares' sums too large");
   const size_t lds = head + std::max({pairs, rho_lds(b, tile), share});
   if (int rc = allow_lds(kern, lds)) return rc;
   hipLaunchKernelGGL(kern, dim3(b.n_walkers), dim3(BLOCK), lds, as_stream(stream), b.d_sys, b.d_walk, pos, state,
-                     energy, jastrow, lds_pos, tile);
+                     energy, jastrow, lds_pos, tile, int(lds - head));
   return last_launch();
 }
 
@@ -784,7 +793,7 @@ int rebuild_launch(const LaunchBatch& b, char* state, void* stream) {
   if (int rc = allow_lds(kern, lds)) return rc;
   const int per = std::max(1, std::min(16, b.n_walkers / 512));
   hipLaunchKernelGGL(kern, dim3((b.n_walkers + per - 1) / per, chunks), dim3(REBUILD_NT), lds, as_stream(stream),
-                     b.d_sys, b.d_walk, state, tile, b.n_walkers, per);
+                     b.d_sys, b.d_walk, state, tile, int(lds), b.n_walkers, per);
   return last_launch();
 }
 

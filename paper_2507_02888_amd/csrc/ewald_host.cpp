@@ -830,6 +830,21 @@ ewald_status ewald_setup(const ewald_sys_desc* desc, ewald_sys** out) try {
     DevSys& D = S->dev;
     D.n_grp = n_grp;
     D.n_ent = off;
+    // A particle's partners in as many shares as make the workgroup's rounds (an
+    // item, a particle's share, per thread) take the fewest groups of four partners,
+    // counting one for an item's own.
+    const int n = S->n_mobile, half = (n - 1) / 2, full = half / 4;
+    const int more = (half - 4 * full + (n & 1 ? 0 : 1) + S->n_fixed + 3) / 4;
+    int best = 0;
+    for (int p = 1; p <= PAIR_PARTS; ++p) {
+      const int per_f = (full + p - 1) / p, per_m = (more + p - 1) / p;
+      const int cost = (n * p + BLOCK - 1) / BLOCK * (per_f + per_m + 1);
+      if (p > 1 && cost >= best) continue;
+      best = cost;
+      D.pair_parts = p;
+      D.pair_full = 4 * per_f;
+      D.pair_more = 4 * per_m;
+    }
     D.ph_hn = hn;
     D.ph_o1 = 16 * (nmax[0] + 1);
     D.ph_ou = D.ph_o1 + (dim == 3 ? 16 * (nmax[1] + 1) : 0);

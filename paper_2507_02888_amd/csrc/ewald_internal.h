@@ -25,6 +25,7 @@ constexpr int GRP_QMAX = 6;       // longest column piece of the rho build, in s
 constexpr size_t GRP_BYTES = size_t(GRP_QMAX) * 64 * 16;  // one group's entries
 constexpr int TILE_MIN = 8;       // fewest particles per phase-table tile that the launchers aim for
 constexpr int TILE_MAX = 64;      // most
+constexpr int PAIR_PARTS = 8;     // most shares of a particle's partners in the energy kernel
 constexpr int RUN_CHUNK = 64;     // proposals staged in LDS per chunk by the fused kernel
 constexpr int WTAB_MAX = 1024;    // largest shell table kept in LDS by the fused kernel
 constexpr int POLY_MAX = 32;      // largest degree of the pair-potential polynomial (FP64)
@@ -130,6 +131,9 @@ struct DevSys {
   // (3D) and of the last dimension at ph_o1 and ph_ou, ph_hn entries in the
   // last, ph_runs runs of 8 entries in the longest row.
   int n_grp, n_ent;  // groups; sum of grp_q
+  // the energy kernel's pair loop: shares of a particle's partners, and the
+  // partners per share of the loop over all particles alike and of the rest
+  int pair_parts, pair_full, pair_more;
   int ph_hn, ph_o1, ph_ou, ph_stride, ph_runs;
   const int32_t* grp_q;
   const int32_t* grp_off;

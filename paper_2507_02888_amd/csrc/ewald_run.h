@@ -63,8 +63,8 @@ __device__ __forceinline__ double run_rebuild(const DevSys* __restrict__ S, cons
   const bool fits = S->n_ent * 1024u <= rc_bytes;
   double drift = 0.0;
   cplx<double>* out = reinterpret_cast<cplx<double>*>(rho);
-  rho_build<DIM, NW, 2>(S, pos, q, n, tabs, tile, reinterpret_cast<cplx<double>*>(tabs), fits ? gs : NW, 0, S->n_grp,
-                        [&](int idx, cplx<double> v, int) {
+  rho_build<DIM, NW, 2, false>(S, [&](int p, int d) { return pos[p * DIM + d]; }, q, n, tabs, tile, reinterpret_cast<cplx<double>*>(tabs), int(rc_bytes),
+                        fits ? gs : NW, 0, S->n_grp, [&](int idx, cplx<double> v, double2) {
                           if (rfix) {
                             v.x += rfix[2 * idx];
                             v.y += rfix[2 * idx + 1];
