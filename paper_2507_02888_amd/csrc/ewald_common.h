@@ -86,28 +86,37 @@ __device__ __forceinline__ double scalar_k(double c, double x) {
   return c;
 }
 
+// SK: the fused kernel, which has no vector registers to spare; the others
+// keep the constants as they come (a step's tables at 512 electrons take 0.2 of its
+// 13 us longer with the moves to scalar registers).
+template <bool SK>
+__device__ __forceinline__ double series_k(double c, double x) {
+  return SK ? scalar_k(c, x) : c;
+}
+
+template <bool SK>
 __device__ __forceinline__ cplx<double> turn(double x) {
   double r;
   int q;
   quarter_turns(x, r, q);
   const double th = r * 1.5707963267948966, t2 = th * th;
-  double sp = scalar_k(2.8114572543455206e-15, th);
-  sp = fma(sp, t2, scalar_k(-7.6471637318198165e-13, th));
-  sp = fma(sp, t2, scalar_k(1.6059043836821613e-10, th));
-  sp = fma(sp, t2, scalar_k(-2.5052108385441720e-08, th));
-  sp = fma(sp, t2, scalar_k(2.7557319223985893e-06, th));
-  sp = fma(sp, t2, scalar_k(-1.9841269841269841e-04, th));
-  sp = fma(sp, t2, scalar_k(8.3333333333333333e-03, th));
-  sp = fma(sp, t2, scalar_k(-1.6666666666666667e-01, th));
+  double sp = series_k<SK>(2.8114572543455206e-15, th);
+  sp = fma(sp, t2, series_k<SK>(-7.6471637318198165e-13, th));
+  sp = fma(sp, t2, series_k<SK>(1.6059043836821613e-10, th));
+  sp = fma(sp, t2, series_k<SK>(-2.5052108385441720e-08, th));
+  sp = fma(sp, t2, series_k<SK>(2.7557319223985893e-06, th));
+  sp = fma(sp, t2, series_k<SK>(-1.9841269841269841e-04, th));
+  sp = fma(sp, t2, series_k<SK>(8.3333333333333333e-03, th));
+  sp = fma(sp, t2, series_k<SK>(-1.6666666666666667e-01, th));
   sp = fma(sp, t2 * th, th);
-  double cp = scalar_k(-1.5619206968586225e-16, th);
-  cp = fma(cp, t2, scalar_k(4.7794773323873853e-14, th));
-  cp = fma(cp, t2, scalar_k(-1.1470745597729725e-11, th));
-  cp = fma(cp, t2, scalar_k(2.0876756987868099e-09, th));
-  cp = fma(cp, t2, scalar_k(-2.7557319223985891e-07, th));
-  cp = fma(cp, t2, scalar_k(2.4801587301587302e-05, th));
-  cp = fma(cp, t2, scalar_k(-1.3888888888888889e-03, th));
-  cp = fma(cp, t2, scalar_k(4.1666666666666667e-02, th));
+  double cp = series_k<SK>(-1.5619206968586225e-16, th);
+  cp = fma(cp, t2, series_k<SK>(4.7794773323873853e-14, th));
+  cp = fma(cp, t2, series_k<SK>(-1.1470745597729725e-11, th));
+  cp = fma(cp, t2, series_k<SK>(2.0876756987868099e-09, th));
+  cp = fma(cp, t2, series_k<SK>(-2.7557319223985891e-07, th));
+  cp = fma(cp, t2, series_k<SK>(2.4801587301587302e-05, th));
+  cp = fma(cp, t2, series_k<SK>(-1.3888888888888889e-03, th));
+  cp = fma(cp, t2, series_k<SK>(4.1666666666666667e-02, th));
   cp = fma(cp, t2, -0.5);
   cp = fma(cp, t2, 1.0);
   return rotate_quarter<double>(cp, sp, q);
@@ -866,13 +875,13 @@ __device__ __forceinline__ cplx<R> ld_at_byte(const cplx<R>* tab, uint32_t byte_
 // One row, by one thread: powers of exp(2 pi i s) formed by repeated FP64
 // multiplication (the paper's buffered powers, Sec. 5.2), with an exact
 // restart every 8 powers so the rounding error stays below ~8 ulp; stored in R.
-template <typename R>
+template <typename R, bool SK>
 __device__ __forceinline__ void fill_row(cplx<R>* row, double s, int nm) {
-  const cplx<double> u = turn(s);
+  const cplx<double> u = turn<SK>(s);
   cplx<double> c = {1.0, 0.0};
   row[nm] = {R(1), R(0)};
   for (int m = 1; m <= nm; ++m) {
-    c = (m & 7) == 0 ? turn(double(m) * s) : cmul(c, u);
+    c = (m & 7) == 0 ? turn<SK>(double(m) * s) : cmul(c, u);
     row[nm + m] = {R(c.x), R(c.y)};
     row[nm - m] = {R(c.x), R(-c.y)};
   }
@@ -980,9 +989,10 @@ __device__ __forceinline__ cplx<double> lds_entry(const char* p) {
 // One run of at most 8 entries of a phase-table row: entry m is
 // scale exp(2 pi i (m + off) s), m = m0 .. min(m0 + 8, m1) - 1, powers from an
 // exactly reduced start (error below ~8 ulp).
+template <bool SK>
 __device__ __forceinline__ void fill_run(char* row, double s, double off, int m0, int m1, double scale) {
-  const cplx<double> u = turn(s);
-  cplx<double> c = turn((double(m0) + off) * s);
+  const cplx<double> u = turn<SK>(s);
+  cplx<double> c = turn<SK>((double(m0) + off) * s);
   c.x *= scale;
   c.y *= scale;
   const int e = min(m0 + 8, m1);
@@ -996,7 +1006,7 @@ __device__ __forceinline__ void fill_run(char* row, double s, double off, int m0
 // four, empty ones, all zero): per particle the rows exp(i n th_d), n = 0 .. nmax[d], of
 // the leading dimensions (the first carries the charge) and
 // exp(i (h + 1/2) th_last), h = 0 .. ph_hn - 1.
-template <int DIM, int NT, typename Pos>
+template <int DIM, int NT, bool SK, typename Pos>
 __device__ __forceinline__ void fill_tables(const DevSys* __restrict__ S, const Pos& frac, const double* q, int p0,
                                             int np, int turn_at, char* tabs) {
   const int runs = S->ph_runs;  // of the longest row
@@ -1012,7 +1022,7 @@ __device__ __forceinline__ void fill_tables(const DevSys* __restrict__ S, const 
     if (m0 >= m1) continue;
     char* t = tabs + pp * stride + off;
     if (pp < np)
-      fill_run(t, frac(p0 + pp, d), last ? 0.5 : 0.0, m0, m1, d == 0 ? q[p0 + pp] : 1.0);
+      fill_run<SK>(t, frac(p0 + pp, d), last ? 0.5 : 0.0, m0, m1, d == 0 ? q[p0 + pp] : 1.0);
     else
       for (int m = m0; m < min(m0 + 8, m1); ++m) *reinterpret_cast<f64x2*>(t + 16 * m) = f64x2{0.0, 0.0};
   }
@@ -1022,7 +1032,7 @@ __device__ __forceinline__ double flip_sign(double v, uint32_t mask) {
   return __hiloint2double(__double2hiint(v) ^ int(mask), __double2loint(v));
 }
 
-template <int DIM, int NW, int NS, bool WGT, typename Pos, typename Sink>
+template <int DIM, int NW, int NS, bool WGT, bool SK, typename Pos, typename Sink>
 __device__ __forceinline__ void rho_build(const DevSys* __restrict__ S, const Pos& frac, const double* q, int n,
                                           char* tabs, int tile, cplx<double>* rc, int rc_bytes, int gw, int g_lo,
                                           int g_hi, Sink&& sink) {
@@ -1054,13 +1064,13 @@ __device__ __forceinline__ void rho_build(const DevSys* __restrict__ S, const Po
 #pragma unroll
       for (int i = 0; i < GRP_QMAX; ++i) ax[t][i] = ay[t][i] = 0.0;
     }
-    fill_tables<DIM, NT>(S, frac, q, 0, min(tile, n), 0, tabs);
+    fill_tables<DIM, NT, SK>(S, frac, q, 0, min(tile, n), 0, tabs);
 #pragma unroll
     for (int t = 0; t < NS; ++t) Q[t] = uniform_i(Q[t]);
     __syncthreads();
     for (int p0 = 0, b = 0; p0 < n; p0 += tile, b ^= 1) {
       const int left = n - p0;
-      if (left > tile) fill_tables<DIM, NT>(S, frac, q, p0 + tile, min(tile, left - tile), p0 + tile, b ? tabs : tabs1);
+      if (left > tile) fill_tables<DIM, NT, SK>(S, frac, q, p0 + tile, min(tile, left - tile), p0 + tile, b ? tabs : tabs1);
       const int np_pad = (min(tile, left) + 3) & ~3;
       // uniform branches on the groups' lengths (Q[1] <= Q[0]: they are
       // sorted); written as a switch, or as loops for every pair of lengths,

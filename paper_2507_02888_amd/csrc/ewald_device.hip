@@ -101,7 +101,7 @@ __global__ __launch_bounds__(BLOCK, UJ || (PD > 16 && ORTHO) ? 3 : 4) void k_ene
   // the tables are built from the arguments, not from spos: one trip to memory
   // before the first tile instead of three in a row
   auto frac = [&](int p, int d) { return to_frac1<DIM>(pw + p * DIM, S->Ainv, d); };
-  rho_build<DIM, BLOCK / 64, 2, true>(S, frac, S->mobile_q, n0, tabs, tile, rc, rc_bytes, gw, 0, S->n_grp,
+  rho_build<DIM, BLOCK / 64, 2, true, false>(S, frac, S->mobile_q, n0, tabs, tile, rc, rc_bytes, gw, 0, S->n_grp,
                                 [&](int idx, cplx<double> v, double2 w2) {
                                   if (nfix > 0) {
                                     v.x += S->rho_fix[2 * idx];
@@ -115,7 +115,7 @@ __global__ __launch_bounds__(BLOCK, UJ || (PD > 16 && ORTHO) ? 3 : 4) void k_ene
   if (lay) {
     __syncthreads();
     double2* rho12 = rho2 + size_t(SEG) * nseg;
-    rho_build<DIM, BLOCK / 64, 2, true>(S, [&](int p, int d) { return frac(n0 + p, d); }, S->mobile_q + n0, n - n0,
+    rho_build<DIM, BLOCK / 64, 2, true, false>(S, [&](int p, int d) { return frac(n0 + p, d); }, S->mobile_q + n0, n - n0,
                                   tabs, tile, rc, rc_bytes, gw, 0, S->n_grp, [&](int idx, cplx<double> v, double2 w2) {
                                     if (nfix > 0) {
                                       v.x += S->rho_fix1[2 * idx];
@@ -368,7 +368,7 @@ __global__ __launch_bounds__(BLOCK, 4) void k_delta(const DevSys* __restrict__ s
       double so_p[DIM];
 #pragma unroll
       for (int d = 0; d < DIM; ++d) so_p[d] = spos[pk * DIM + d];
-      if (tid < 2 * DIM) fill_row<R>(tpo + tid * tbl, pick_coord<DIM>(so_p, sp, tid), nm);
+      if (tid < 2 * DIM) fill_row<R, false>(tpo + tid * tbl, pick_coord<DIM>(so_p, sp, tid), nm);
       __syncthreads();
       accept_stream<DIM, R>(S, tpo, tpn, rho + lp * plane, qp);
     }
@@ -419,12 +419,12 @@ __global__ __launch_bounds__(BLOCK, 4) void k_delta(const DevSys* __restrict__ s
     }
   }
   const double qk = S->mobile_q[k];
-  if (tid < 2 * DIM) fill_row<R>(to + tid * tbl, pick_coord<DIM>(so, sn, tid), nm);  // to, then tn
+  if (tid < 2 * DIM) fill_row<R, false>(to + tid * tbl, pick_coord<DIM>(so, sn, tid), nm);  // to, then tn
   if (acc && tid >= 2 * DIM && tid < 4 * DIM) {
     double so_p[DIM];
 #pragma unroll
     for (int d = 0; d < DIM; ++d) so_p[d] = spos[pk * DIM + d];
-    fill_row<R>(tpo + (tid - 2 * DIM) * tbl, pick_coord<DIM>(so_p, sp, tid - 2 * DIM), nm);  // tpo, then tpn
+    fill_row<R, false>(tpo + (tid - 2 * DIM) * tbl, pick_coord<DIM>(so_p, sp, tid - 2 * DIM), nm);  // tpo, then tpn
   }
   __syncthreads();
 
@@ -622,7 +622,7 @@ __global__ __launch_bounds__(BLOCK) void k_accept(const DevSys* __restrict__ sys
       so[d] = spos[pk * DIM + d];
       sn[d] = hdr->pending_s[d];
     }
-    if (tid < 2 * DIM) fill_row<R>(to + tid * tbl, pick_coord<DIM>(so, sn, tid), nm);  // to, then tn
+    if (tid < 2 * DIM) fill_row<R, false>(to + tid * tbl, pick_coord<DIM>(so, sn, tid), nm);  // to, then tn
   }
   __syncthreads();  // every thread has read the header and pending position
   if (acc) {
@@ -682,7 +682,7 @@ __global__ __launch_bounds__(REBUILD_NT) void k_rebuild(const DevSys* __restrict
     double2* rl = reinterpret_cast<double2*>(rho) + size_t(SEG) * nseg * l;
     const double* rfix = S->n_fixed > 0 ? (l == 0 ? S->rho_fix : S->rho_fix1) : nullptr;
     // the waves' shares meet in the tables' LDS (one pass, after their last use)
-    rho_build<DIM, REBUILD_NT / 64, 1, false>(S, [&](int p, int d) { return spos[(p0 + p) * DIM + d]; },
+    rho_build<DIM, REBUILD_NT / 64, 1, false, false>(S, [&](int p, int d) { return spos[(p0 + p) * DIM + d]; },
                                        S->mobile_q + p0, p1 - p0, tabs, tile, reinterpret_cast<cplx<double>*>(smem), rc_bytes, gw, g_lo, g_hi,
                                        [&](int idx, cplx<double> v, double2) {
                                          if (rfix) {

@@ -63,7 +63,7 @@ __device__ __forceinline__ double run_rebuild(const DevSys* __restrict__ S, cons
   const bool fits = S->n_ent * 1024u <= rc_bytes;
   double drift = 0.0;
   cplx<double>* out = reinterpret_cast<cplx<double>*>(rho);
-  rho_build<DIM, NW, 2, false>(S, [&](int p, int d) { return pos[p * DIM + d]; }, q, n, tabs, tile, reinterpret_cast<cplx<double>*>(tabs), int(rc_bytes),
+  rho_build<DIM, NW, 2, false, true>(S, [&](int p, int d) { return pos[p * DIM + d]; }, q, n, tabs, tile, reinterpret_cast<cplx<double>*>(tabs), int(rc_bytes),
                         fits ? gs : NW, 0, S->n_grp, [&](int idx, cplx<double> v, double2) {
                           if (rfix) {
                             v.x += rfix[2 * idx];
@@ -349,7 +349,7 @@ __global__ __launch_bounds__(NT, NT >= 1024 ? 4 : WV) void k_run(const DevSys* _
       const int e = e0 + tid;
       const int q = e / (2 * DIM), r = e - q * (2 * DIM);
       if (e < len * 2 * DIM && sk[q] >= 0)
-        fill_row<R>(ctab + e * tbl, r < DIM ? st_so[q * DIM + r] : st_sn[q * DIM + r - DIM], nm);
+        fill_row<R, true>(ctab + e * tbl, r < DIM ? st_so[q * DIM + r] : st_sn[q * DIM + r - DIM], nm);
     }
     __syncthreads();
 
