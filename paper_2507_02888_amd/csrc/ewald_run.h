@@ -754,20 +754,24 @@ inline int run_shape(int max_n_seg, int max_particles, int threads, int* nt, int
 // and 0.81, FP64 0.86 and 0.70; hexagonal 2048 x 512 FP64 2.30 and 1.85, mixed 2.92
 // and 2.02; diamond 4096 x 256 mixed 4.96 and 3.68, FP64 4.08 and 3.28; bilayer
 // 2048 x 512 mixed 3.42 and 2.47.
+// The derivative kernels with the u term spill at more than two waves and stay there
+// (128 moves, ms at two, three and four: 17 electrons, 2265 walkers mixed 1.66, 2.56,
+// 3.25; 250, 1024 walkers FP64 0.92, 1.14, 1.40; without the u term mixed 0.75, 0.76, 0.66).
 // 512 < s <= 1024: two workgroups of 512 threads at four waves take 1.6 to 1.75
 // times the round of one of 1024 (N = 1024, 1024 walkers x 256 moves FP64: 1.94 and
 // 2.23 ms).  The derivative kernels run one workgroup of 512 threads with 256
 // registers per lane whatever the batch (with the u term and 128 moves: 1024
 // walkers 3.0 ms and 8 walkers 0.71; at 1024 threads, which spill, 3.5 and 0.84).  Walkers of more particles than the registers
 // hold, or with ions, keep 1024 threads.
-inline void run_defaults(const LaunchBatch& b, bool der, int* threads, int* waves) {
+inline void run_defaults(const LaunchBatch& b, int jm, int* threads, int* waves) {
+  const bool der = jm == 2 || jm == 4;
   *threads = b.run_threads;
   *waves = b.run_waves;
   if (*waves != 0 || b.run_wpb > 0) return;
   auto rounds = [&](int per_cu) { return (b.n_walkers + per_cu * b.n_cu - 1) / (per_cu * b.n_cu); };
   int nt = 0, spt = 0, ppr = 0;
   if (!run_shape(b.max_n_seg, b.max_particles, *threads, &nt, &spt, &ppr)) return;
-  if (nt == 256) {
+  if (nt == 256 && jm != 4) {
     const double t2 = rounds(2), t3 = rounds(3) * 1.25, t4 = rounds(4) * 1.5;
     *waves = t2 <= t3 && t2 <= t4 ? 2 : t4 <= t3 ? 4 : 3;
   } else if (nt == 1024 && *threads == 0 && b.max_n_seg > 512 && b.max_particles > 512 && b.max_particles <= 1024 &&
@@ -781,7 +785,7 @@ template <int DIM, bool MIXED, int JM, int PD, bool ORTHO, bool LAY = false>
 int run_jp(const LaunchBatch& b, const RunArgs& a) {
   static_assert(RUN_CHUNK <= 256, "staging uses one thread per move");
   int nt = 0, spt = 0, ppr = 0, threads = 0, waves = 0;
-  run_defaults(b, JM == 2 || JM == 4, &threads, &waves);
+  run_defaults(b, JM, &threads, &waves);
   if (!run_shape(b.max_n_seg, b.max_particles, threads, &nt, &spt, &ppr)) return RUN_NO_FIT;
   // XTRA: particles beyond the registers' share, or fixed ions, in some
   // walker.  Leaving those loops out pays at 512 and 1024 threads; the
