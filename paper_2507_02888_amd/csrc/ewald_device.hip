@@ -993,7 +993,17 @@ int dev_alloc(void** p, size_t bytes) {
   hipError_t e = hipMalloc(p, bytes);
   return e == hipSuccess ? 0 : int(e);
 }
-int dev_free(void* p) { return int(hipFree(p)); }
+// Handles are dropped at any time (by a garbage collector, or on another thread),
+// also while a stream is being captured.  hipFree is then refused, and the
+// capture invalidated, unless the calling thread's capture mode is relaxed: the
+// mode is exchanged for the call.
+int dev_free(void* p) {
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  const hipError_t x = hipThreadExchangeStreamCaptureMode(&mode);
+  const hipError_t e = hipFree(p);
+  if (x == hipSuccess) (void)hipThreadExchangeStreamCaptureMode(&mode);
+  return int(e);
+}
 int dev_upload(void* dst, const void* src, size_t bytes) {
   hipError_t e = hipMemcpy(dst, src, bytes, hipMemcpyHostToDevice);
   return e == hipSuccess ? 0 : int(e);
