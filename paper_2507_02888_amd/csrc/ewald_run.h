@@ -725,9 +725,10 @@ int run_inst(const LaunchBatch& b, const RunArgs& a) {
 // lane) were measured slower than 256 x 2 on the 250-, 300- and uneven
 // 64..512-electron workloads: at ~200 registers per lane such a kernel fits
 // one workgroup per CU, where 256-thread ones fit two.
-// Particles per thread in registers: 1 when the largest walker has at most
-// NT particles (always with 1024 threads, where larger walkers' remaining
-// particles are read from LDS), else 2.
+// Particles per thread in registers: 1 with 1024 threads (larger walkers' remaining
+// particles are read from LDS) and with 256 threads where the largest walker
+// has at most 256 particles, else 2 (512 threads: always, smaller walkers
+// leaving the second place empty, which a wave skips as a whole).
 inline int run_shape(int max_n_seg, int max_particles, int threads, int* nt, int* spt, int* ppr) {
   struct Shape { int nt, spt; };
   static const Shape shapes[] = {{256, 1}, {256, 2}, {1024, 1}, {512, 2}, {512, 4}};
@@ -737,7 +738,7 @@ inline int run_shape(int max_n_seg, int max_particles, int threads, int* nt, int
     if (threads == 0 || threads == sh.nt) {
       *nt = sh.nt;
       *spt = sh.spt;
-      *ppr = (sh.nt >= 1024 || max_particles <= sh.nt) ? 1 : 2;
+      *ppr = (sh.nt == 1024 || (sh.nt == 256 && max_particles <= sh.nt)) ? 1 : 2;
       return 1;
     }
   }
