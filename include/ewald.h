@@ -398,8 +398,12 @@ void ewald_blip_destroy(ewald_blip *b);
  *   val   device out [n_points][n_orb]
  *   grad  device out [n_points][3][n_orb] (Cartesian), or NULL
  *   lap   device out [n_points][n_orb], or NULL (both or neither)
- * FP64 throughout.  Enqueues one kernel on `stream`; no allocation, no
- * synchronisation (graph-capturable).  Status: E_ARG, E_HIP. */
+ * FP64 throughout.  Enqueues kernels on `stream` (one; six for a large batch,
+ * which is first put in the order of the points' places on the grid); no
+ * allocation, no synchronisation (graph-capturable).  The order is kept in the
+ * last part of val until the values there are written: val must not overlap
+ * coef or pos, nor be read by other streams before the call's work is done.
+ * Status: E_ARG, E_HIP. */
 ewald_status ewald_blip_eval_batch(const ewald_blip *b, const double *coef, int n_points, const double *pos,
                                    double *val, double *grad, double *lap, void *stream);
 

@@ -7,12 +7,16 @@
 // the orbitals:
 //   - lane p < 64 finds grid point p of the 4 x 4 x 4 window around the
 //     point and forms its blip product, the product's Cartesian gradient and
-//     its Laplacian (five weights), kept in registers with the row index;
+//     its Laplacian (five weights), parked in LDS;
 //   - the wave then streams the 64 coefficient rows (orbital index fastest),
-//     each row's weights read from their lane into scalar registers, and
-//     accumulates value, gradient and Laplacian of the lane's orbitals.
-//     (Read back from LDS, a row's weights cost more LDS cycles, 20 per row
-//     and wave, than their multiply-adds on four orbitals per lane.)
+//     eight in flight, each row's address read from its lane into scalar
+//     registers and its weights from LDS, and accumulates value, gradient and
+//     Laplacian of the lane's orbitals.
+// (Weights read from their lanes as well, ten reads per row, spare the LDS but
+// cost more vector issue than they save: 40,000 points, gradients, 33 orbitals 156 us against
+// 94; 130 orbitals 341 and 209; 512 on a 40^3 grid in the order below 707 and
+// 505.  One wave for all orbitals of a point takes 512 orbitals at 500
+// points 54 us, a wave per slice 16.)
 // The work is a gather of 64 n_orb coefficients per point with 5 FMAs per
 // coefficient, not a dense contraction (each point takes its own 64 rows),
 // bound by where the rows come from.  Points in any order take every row from
@@ -20,9 +24,7 @@
 // over a coefficient set beyond the L2s is therefore served in the order of
 // the points' places on the grid (bricks of BRICK^3 cells, each L2 taking a
 // contiguous range), so that the points that share a row (64 windows of the
-// grid hold it) find it in the L2: 65,536 points of 512 orbitals on a 40^3 grid
-// take 1.04 ms (16.6 TB/s of rows) where they took 2.48 ms (7.0 TB/s, weights
-// read from LDS).  The multiply-adds alone are 0.3 ms.
+// grid hold it) find it in the L2.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -78,10 +80,10 @@ constexpr int BLIP_WAVES = 4;  // waves per workgroup
 constexpr int BRICK = 4;       // cells along each side of a brick (ordering of large batches)
 constexpr int BRICKS_MAX = 16384;
 
-__device__ __forceinline__ double lane_value(double v, int r) {
-  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), r),
-                          __builtin_amdgcn_readlane(__double2loint(v), r));
-}
+struct __align__(16) BlipW {
+  double b, gx, gy, gz, l;
+  double pad_;
+};
 
 // A point's grid coordinates x_d = n_d s_d, s wrapped into [0, 1).
 __device__ __forceinline__ void grid_coords(const BlipK& K, const double* __restrict__ pos, size_t p, double* x) {
@@ -96,15 +98,16 @@ __device__ __forceinline__ void grid_coords(const BlipK& K, const double* __rest
 }
 
 // VW = 2: orbital pairs read as 16-byte loads (n_orb even); 1: single loads.
-// NV: vectors of VW orbitals per lane; a wave serves 64 VW NV orbitals of one
-// point and `slices` waves (consecutive, so that they run together) all of them.
+// A wave serves 64 VW orbitals of one point and `slices` waves (consecutive, so
+// that they run together) all of them.
 // order: NULL (points p_lo .. p_hi - 1 in turn), or the points' order; those
 // from p_hi on are left to a later launch (their outputs hold the order).
-template <int VW, int NV, bool DER>
-__global__ __launch_bounds__(64 * BLIP_WAVES, 4) void k_blip(BlipK K, const double* __restrict__ coef, int p_lo, int p_hi,
+template <int VW, bool DER>
+__global__ __launch_bounds__(64 * BLIP_WAVES) void k_blip(BlipK K, const double* __restrict__ coef, int p_lo, int p_hi,
                                                             int n_items, int slices,
                                                             const int* order, const double* __restrict__ pos,
                                                             double* val, double* grad, double* lap) {
+  __shared__ BlipW wts[BLIP_WAVES][64];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
   int blk = blockIdx.x;
   if (order) {
@@ -119,7 +122,7 @@ __global__ __launch_bounds__(64 * BLIP_WAVES, 4) void k_blip(BlipK K, const doub
   const int p = order ? __builtin_amdgcn_readfirstlane(order[it]) : p_lo + it;
   if (p >= p_hi) return;
   const int n_orb = K.n_orb;
-  double wb, wx = 0.0, wy = 0.0, wz = 0.0, wl = 0.0;
+  BlipW* W = wts[wave];
   uint64_t row;  // byte offset of the lane's coefficient row
   {
     double x[3];
@@ -135,7 +138,8 @@ __global__ __launch_bounds__(64 * BLIP_WAVES, 4) void k_blip(BlipK K, const doub
       const int gw = g % K.n[d];
       idx[d] = gw < 0 ? gw + K.n[d] : gw;
     }
-    wb = f[0] * f[1] * f[2];
+    BlipW w;
+    w.b = f[0] * f[1] * f[2];
     if (DER) {
       const double dx[3] = {f1[0] * f[1] * f[2], f[0] * f1[1] * f[2], f[0] * f[1] * f1[2]};
       // second derivatives in x: diagonal and mixed
@@ -144,91 +148,78 @@ __global__ __launch_bounds__(64 * BLIP_WAVES, 4) void k_blip(BlipK K, const doub
       double g[3];
 #pragma unroll
       for (int e = 0; e < 3; ++e) g[e] = fma(K.J[e * 3 + 2], dx[2], fma(K.J[e * 3 + 1], dx[1], K.J[e * 3] * dx[0]));
-      wx = g[0];
-      wy = g[1];
-      wz = g[2];
-      wl = fma(K.M[0], h00, fma(K.M[1], h11, fma(K.M[2], h22,
-           2.0 * fma(K.M[3], h01, fma(K.M[4], h02, K.M[5] * h12)))));
+      w.gx = g[0];
+      w.gy = g[1];
+      w.gz = g[2];
+      w.l = fma(K.M[0], h00, fma(K.M[1], h11, fma(K.M[2], h22,
+            2.0 * fma(K.M[3], h01, fma(K.M[4], h02, K.M[5] * h12)))));
+    } else {
+      w.gx = w.gy = w.gz = w.l = 0.0;
     }
+    w.pad_ = 0.0;
+    W[lane] = w;
     row = ((uint64_t(idx[0]) * uint32_t(K.n[1]) + uint32_t(idx[1])) * uint32_t(K.n[2]) + uint32_t(idx[2])) * uint32_t(n_orb) * 8;
   }
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   const size_t out0 = size_t(p) * n_orb;
-  constexpr int SLICE = 64 * VW * NV;
-  for (int o0 = slice * SLICE; o0 < n_orb; o0 += slices * SLICE) {
-    // opaque per pass: 640 broadcast registers are not to be kept for a next one
-    asm volatile("" : "+v"(wb), "+v"(wx), "+v"(wy), "+v"(wz), "+v"(wl));
-    double v[NV][VW], gx[NV][VW], gy[NV][VW], gz[NV][VW], l[NV][VW];
-    int oo[NV];  // the lane's orbitals (clamped: every load is in bounds)
+  for (int o0 = slice * 64 * VW; o0 < n_orb; o0 += slices * 64 * VW) {
+    double v[VW], gx[VW], gy[VW], gz[VW], l[VW];
+    const int o = o0 + lane * VW;
+    const int oo = o < n_orb ? o : 0;  // (clamped: every load is in bounds)
 #pragma unroll
-    for (int i = 0; i < NV; ++i) {
-      const int o = o0 + (i * 64 + lane) * VW;
-      oo[i] = o < n_orb ? o : 0;
-#pragma unroll
-      for (int c = 0; c < VW; ++c) v[i][c] = gx[i][c] = gy[i][c] = gz[i][c] = l[i][c] = 0.0;
-    }
+    for (int c = 0; c < VW; ++c) v[c] = gx[c] = gy[c] = gz[c] = l[c] = 0.0;
     constexpr int RB = 8;  // rows in flight
 #pragma unroll 1
     for (int r0 = 0; r0 < 64; r0 += RB) {
-      double a[RB][NV][VW];
+      double a[RB][VW];
 #pragma unroll
       for (int r = 0; r < RB; ++r) {
         const uint64_t at = uint64_t(uint32_t(__builtin_amdgcn_readlane(int(row >> 32), r0 + r))) << 32 |
                             uint32_t(__builtin_amdgcn_readlane(int(uint32_t(row)), r0 + r));
         const double* src = reinterpret_cast<const double*>(reinterpret_cast<const char*>(coef) + at);
-#pragma unroll
-        for (int i = 0; i < NV; ++i) {
-          if (VW == 2) {
-            const double2 t = *reinterpret_cast<const double2*>(src + oo[i]);
-            a[r][i][0] = t.x;
-            a[r][i][VW - 1] = t.y;
-          } else {
-            a[r][i][0] = src[oo[i]];
-          }
+        if (VW == 2) {
+          const double2 t = *reinterpret_cast<const double2*>(src + oo);
+          a[r][0] = t.x;
+          a[r][VW - 1] = t.y;
+        } else {
+          a[r][0] = src[oo];
         }
       }
 #pragma unroll
       for (int r = 0; r < RB; ++r) {
-        const double sb = lane_value(wb, r0 + r);
-        double sx = 0.0, sy = 0.0, sz = 0.0, sl = 0.0;
-        if (DER) {
-          sx = lane_value(wx, r0 + r);
-          sy = lane_value(wy, r0 + r);
-          sz = lane_value(wz, r0 + r);
-          sl = lane_value(wl, r0 + r);
-        }
-#pragma unroll
-        for (int i = 0; i < NV; ++i)
-#pragma unroll
-          for (int c = 0; c < VW; ++c) {
-            v[i][c] = fma(sb, a[r][i][c], v[i][c]);
-            if (DER) {
-              gx[i][c] = fma(sx, a[r][i][c], gx[i][c]);
-              gy[i][c] = fma(sy, a[r][i][c], gy[i][c]);
-              gz[i][c] = fma(sz, a[r][i][c], gz[i][c]);
-              l[i][c] = fma(sl, a[r][i][c], l[i][c]);
-            }
-          }
-      }
-    }
-#pragma unroll
-    for (int i = 0; i < NV; ++i) {
-      const int o = o0 + (i * 64 + lane) * VW;
-      if (o < n_orb)
+        const BlipW w = W[r0 + r];
 #pragma unroll
         for (int c = 0; c < VW; ++c) {
-          val[out0 + o + c] = v[i][c];
+          v[c] = fma(w.b, a[r][c], v[c]);
           if (DER) {
-            grad[3 * out0 + o + c] = gx[i][c];
-            grad[3 * out0 + n_orb + o + c] = gy[i][c];
-            grad[3 * out0 + 2 * size_t(n_orb) + o + c] = gz[i][c];
-            lap[out0 + o + c] = l[i][c];
+            gx[c] = fma(w.gx, a[r][c], gx[c]);
+            gy[c] = fma(w.gy, a[r][c], gy[c]);
+            gz[c] = fma(w.gz, a[r][c], gz[c]);
+            l[c] = fma(w.l, a[r][c], l[c]);
           }
         }
+      }
     }
+    if (o < n_orb)
+#pragma unroll
+      for (int c = 0; c < VW; ++c) {
+        val[out0 + o + c] = v[c];
+        if (DER) {
+          grad[3 * out0 + o + c] = gx[c];
+          grad[3 * out0 + n_orb + o + c] = gy[c];
+          grad[3 * out0 + 2 * size_t(n_orb) + o + c] = gz[c];
+          lap[out0 + o + c] = l[c];
+        }
+      }
   }
 }
 
 // ---- ordering of a large batch by brick: a counting sort ----------------------
+// Workgroups of 1024 points count in LDS first and add each brick's count to
+// the batch's once (points in one brick would otherwise queue up at one address,
+// 12 ns each: 40,000 of them took 1 ms).  Dynamic LDS: one int per brick.
 
 struct Bricks {
   int n[3];  // bricks along each axis
@@ -253,9 +244,18 @@ __global__ void k_brick_zero(int* count, int n) {
   if (i < n) count[i] = 0;
 }
 
-__global__ void k_brick_count(BlipK K, Bricks B, const double* __restrict__ pos, int n_pts, int* count) {
-  const int p = blockIdx.x * blockDim.x + threadIdx.x;
-  if (p < n_pts) atomicAdd(&count[brick_of(K, B, pos, size_t(p))], 1);
+constexpr int SORT_NT = 1024;
+
+__global__ __launch_bounds__(SORT_NT) void k_brick_count(BlipK K, Bricks B, const double* __restrict__ pos, int n_pts,
+                                                         int* count) {
+  extern __shared__ int own[];
+  for (int i = threadIdx.x; i < B.total; i += SORT_NT) own[i] = 0;
+  __syncthreads();
+  const int p = blockIdx.x * SORT_NT + threadIdx.x;
+  if (p < n_pts) atomicAdd(&own[brick_of(K, B, pos, size_t(p))], 1);
+  __syncthreads();
+  for (int i = threadIdx.x; i < B.total; i += SORT_NT)
+    if (own[i] != 0) atomicAdd(&count[i], own[i]);
 }
 
 // Counts to first places, by one workgroup of 1024.
@@ -281,20 +281,28 @@ __global__ __launch_bounds__(1024) void k_brick_scan(int* count, int n) {
 }
 
 // (points of one brick come in any order: no output depends on it)
-__global__ void k_brick_place(BlipK K, Bricks B, const double* __restrict__ pos, int n_pts, int* first, int* order) {
-  const int p = blockIdx.x * blockDim.x + threadIdx.x;
-  if (p < n_pts) order[atomicAdd(&first[brick_of(K, B, pos, size_t(p))], 1)] = p;
+__global__ __launch_bounds__(SORT_NT) void k_brick_place(BlipK K, Bricks B, const double* __restrict__ pos, int n_pts,
+                                                         int* first, int* order) {
+  extern __shared__ int own[];
+  for (int i = threadIdx.x; i < B.total; i += SORT_NT) own[i] = 0;
+  __syncthreads();
+  const int p = blockIdx.x * SORT_NT + threadIdx.x;
+  int b = 0, rank = 0;
+  if (p < n_pts) {
+    b = brick_of(K, B, pos, size_t(p));
+    rank = atomicAdd(&own[b], 1);
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < B.total; i += SORT_NT)
+    if (own[i] != 0) own[i] = atomicAdd(&first[i], own[i]);
+  __syncthreads();
+  if (p < n_pts) order[own[b] + rank] = p;
 }
 
 // One launch over `count` points (order: of all of them; else p_lo, p_lo + 1, ...).
-// Vectors per lane: two where the orbitals fill them (the weights' broadcast, ten
-// lane reads per row, is shared by more orbitals), one for few points or orbitals
-// (more waves).
 void blip_launch(const BlipK& K, bool vec, bool der, const double* coef, int p_lo, int p_hi, int count,
                  const int* order, const double* pos, double* val, double* grad, double* lap, hipStream_t s) {
-  const int vw = vec ? 2 : 1;
-  const bool wide = K.n_orb >= 128 * vw && count >= 2048;
-  const int per = 64 * vw * (wide ? 2 : 1);
+  const int per = vec ? 128 : 64;
   const int slices = (K.n_orb + per - 1) / per;
   const long long items = (long long)count * slices;
   // several passes over the orbitals per wave where the items would not fit the grid
@@ -302,21 +310,13 @@ void blip_launch(const BlipK& K, bool vec, bool der, const double* coef, int p_l
   const int n_items = count * sl;
   int grid = (n_items + BLIP_WAVES - 1) / BLIP_WAVES;
   if (order) grid = (grid + 7) & ~7;
-#define EW_BLIP(VW, NV, DER)                                                                                          \
-  hipLaunchKernelGGL((k_blip<VW, NV, DER>), dim3(grid), dim3(64 * BLIP_WAVES), 0, s, K, coef, p_lo, p_hi, n_items, sl, \
+#define EW_BLIP(VW, DER)                                                                                          \
+  hipLaunchKernelGGL((k_blip<VW, DER>), dim3(grid), dim3(64 * BLIP_WAVES), 0, s, K, coef, p_lo, p_hi, n_items, sl, \
                      order, pos, val, grad, lap)
   if (vec) {
-    if (wide) {
-      if (der) EW_BLIP(2, 2, true); else EW_BLIP(2, 2, false);
-    } else {
-      if (der) EW_BLIP(2, 1, true); else EW_BLIP(2, 1, false);
-    }
+    if (der) EW_BLIP(2, true); else EW_BLIP(2, false);
   } else {
-    if (wide) {
-      if (der) EW_BLIP(1, 2, true); else EW_BLIP(1, 2, false);
-    } else {
-      if (der) EW_BLIP(1, 1, true); else EW_BLIP(1, 1, false);
-    }
+    if (der) EW_BLIP(1, true); else EW_BLIP(1, false);
   }
 #undef EW_BLIP
 }
@@ -414,16 +414,22 @@ ewald_status ewald_blip_eval_batch(const ewald_blip* b, const double* coef, int 
   hipStream_t s = static_cast<hipStream_t>(stream);
   const bool der = grad != nullptr;
   // Ordered where the coefficients exceed the L2s (4 MB each, and a row that
-  // one of them holds is shared by points that all run there) and the points
-  // are enough for rows to be shared; the order (one int per point and per
+  // one of them holds is shared by points that all run there), the points
+  // are enough for rows to be shared and the gather is long enough for the sort's
+  // five launches (20 to 35 us).  Spread points, us without and with the order: 128
+  // orbitals, 10,000 points on 40^3 (0.66 GB of rows) 95 and 66, 256 on 24^3, 4000 points
+  // (0.52 GB), values 66 and 44; 100 orbitals, 4000 points (0.2 GB) 33 and 52.  Points
+  // that all lie in a few bricks find their rows in the L2s anyway and pay for the sort
+  // (10,000 points, 256 orbitals 63 and 87, 40,000 points, 512 orbitals 480 and 500).  The order (one int per point and per
   // brick) sits at the end of `val` until the main launch has read it, and the
-  // points whose values lie there are evaluated last.  16 orbitals at least
-  // keep these few.
+  // points whose values lie there are evaluated last.  48 orbitals at least
+  // keep these few (and shorter rows gain nothing: 33 orbitals, 65,536 points 147 us
+  // and 174).
   const double rows = double(b->grid[0]) * b->grid[1] * b->grid[2];
   ewald::Bricks B;
   for (int d = 0; d < 3; ++d) B.n[d] = (b->grid[d] + ewald::BRICK - 1) / ewald::BRICK;
-  const bool ordered = rows * b->n_orb * 8.0 > 16e6 && b->n_orb >= 16 && n_points >= 2048 && n_points >= rows / 16 &&
-                       double(B.n[0]) * B.n[1] * B.n[2] <= ewald::BRICKS_MAX;
+  const bool ordered = rows * b->n_orb * 8.0 > 16e6 && b->n_orb >= 48 && n_points >= 2048 && n_points >= rows / 16 &&
+                       512.0 * n_points * b->n_orb >= 0.5e9 && double(B.n[0]) * B.n[1] * B.n[2] <= ewald::BRICKS_MAX;
   if (ordered) {
     B.total = B.n[0] * B.n[1] * B.n[2];
     const size_t ints = size_t(n_points) + size_t(B.total);
@@ -432,11 +438,12 @@ ewald_status ewald_blip_eval_batch(const ewald_blip* b, const double* coef, int 
       const int p_hi = n_points - late;
       int* count = reinterpret_cast<int*>(val + size_t(p_hi) * b->n_orb);
       int* order = count + B.total;
-      const dim3 per_point((n_points + 255) / 256);
+      const dim3 sort_grid((n_points + ewald::SORT_NT - 1) / ewald::SORT_NT), sort_block(ewald::SORT_NT);
+      const size_t sort_lds = size_t(B.total) * sizeof(int);
       hipLaunchKernelGGL(ewald::k_brick_zero, dim3((B.total + 255) / 256), dim3(256), 0, s, count, B.total);
-      hipLaunchKernelGGL(ewald::k_brick_count, per_point, dim3(256), 0, s, K, B, pos, n_points, count);
+      hipLaunchKernelGGL(ewald::k_brick_count, sort_grid, sort_block, sort_lds, s, K, B, pos, n_points, count);
       hipLaunchKernelGGL(ewald::k_brick_scan, dim3(1), dim3(1024), 0, s, count, B.total);
-      hipLaunchKernelGGL(ewald::k_brick_place, per_point, dim3(256), 0, s, K, B, pos, n_points, count, order);
+      hipLaunchKernelGGL(ewald::k_brick_place, sort_grid, sort_block, sort_lds, s, K, B, pos, n_points, count, order);
       ewald::blip_launch(K, vec, der, coef, 0, p_hi, n_points, order, pos, val, grad, lap, s);
       ewald::blip_launch(K, vec, der, coef, p_hi, n_points, late, nullptr, pos, val, grad, lap, s);
     } else {
