@@ -317,14 +317,17 @@ ewald_status ewald_run_moves_grad_batch(ewald_batch *b, void *state, int n_steps
  *                  applies to ewald_energy_batch as well
  *   waves          waves per SIMD the kernel is compiled for, for workgroups
  *                  of 256 and 512 threads: 0 = chosen by the walkers per CU
- *                  (2 in the queue mode and at 512 threads), 2 = 256 registers
+ *                  (2 in the queue mode, and with threads = 512; with
+ *                  threads = 0 the default 512 x 2 runs at 4), 2 = 256 registers
  *                  per lane, constants in vector registers, 3 or 4 = more
  *                  workgroups per CU with the constants in scalar registers
  *                  (256 threads: 3 or 4; 512 threads with 2 segments per
  *                  thread: 4); other combinations give E_ARG (1024-thread
  *                  workgroups run at four waves per SIMD by construction).
- *                  The Jastrow-derivative sweep (ewald_run_moves_grad_batch)
- *                  runs 512 x 2 at two waves whatever this says
+ *                  An upper bound for the Jastrow-derivative sweep
+ *                  (ewald_run_moves_grad_batch), whose kernels need more
+ *                  registers: 512 threads and, with the u term, 256 threads run
+ *                  at 2; FP64 in 3D with 2 segments per 256 threads at 3 at most
  *   walkers_per_block  0 = one workgroup per walker, dispatched by the
  *                  hardware in the batch's launch order (most expensive
  *                  walker first); W > 0 = ceil(n_walkers / W) workgroups,
@@ -336,18 +339,24 @@ ewald_status ewald_run_moves_grad_batch(ewald_batch *b, void *state, int n_steps
  *                  E_ARG if negative, or if > 0 with waves 3 or 4 (the
  *                  queue-mode kernels are compiled for two waves per SIMD)
  * Results do not depend on the choice beyond rounding order (the queue mode
- * computes each walker exactly as one workgroup per walker does).  Not to be
- * called concurrently with launches on the same batch. */
+ * computes each walker exactly as one workgroup per walker does).  With
+ * threads = 0 the choice, and so the rounding of a walker's results, may depend
+ * on how many walkers the batch has: a population that is split over several
+ * batches or devices repeats a single batch's results bit for bit only with
+ * threads fixed.  Not to be called concurrently with launches on the same batch. */
 ewald_status ewald_batch_set_tuning(ewald_batch *b, int threads, int chunk, int general_frame, int waves,
                                     int walkers_per_block);
 
-/* The launch shape ewald_run_moves_batch will use: workgroup size, moves per
+/* The launch shape ewald_run_moves_batch will use (without derivative outputs;
+ * ewald_run_moves_grad_batch may take another): workgroup size, moves per
  * chunk, frame (1 = general), fused = 0 when the walkers do not fit the
  * fused kernel's LDS layout (then it runs the per-step
  * kernels in turn), and the waves per SIMD a 256- or 512-thread kernel is
  * compiled for (0 for 1024 threads and when not fused), and the walkers
  * per workgroup (0: one workgroup per walker, and when not fused), so that
- * the values can be passed back to ewald_batch_set_tuning.
+ * the values can be passed back to ewald_batch_set_tuning.  (To pass a
+ * walkers_per_block > 0 with the other values, give waves = 0: the waves of an
+ * untouched batch may be 3 or 4, which the queue mode does not have.)
  * Any output pointer may be NULL. */
 ewald_status ewald_batch_get_tuning(ewald_batch *b, int *threads, int *chunk, int *general_frame,
                                     int *fused, int *waves, int *walkers_per_block);

@@ -1223,6 +1223,9 @@ inline int even(int x) { return (x + 1) & ~1; }
 inline size_t up16(size_t x) { return (x + 15) & ~size_t(15); }
 
 constexpr size_t RUN_LDS_BUDGET = 160 * 1024;  // LDS per workgroup on gfx950
+// LDS that each of per_cu workgroups on a CU may take: it is given out in blocks of
+// 1280 bytes (a third of 160 KB to the byte lets two workgroups run, not three).
+inline size_t lds_share(int per_cu) { return RUN_LDS_BUDGET / 1280 / size_t(per_cu) * 1280; }
 constexpr int RUN_NO_FIT = -1;                 // the fused kernel's LDS does not fit: use the per-step kernels
 
 // Particles per phase-table tile of rho_build with its tiles within `bytes` of

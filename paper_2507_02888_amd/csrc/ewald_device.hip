@@ -718,7 +718,7 @@ int energy_inst(const LaunchBatch& b, const double* pos, char* state, double* en
   // large as LDS allows without lowering the workgroups per CU that
   // registers allow (three or four)
   static const int per_cu = blocks_per_cu(kern, BLOCK);
-  const size_t budget = RUN_LDS_BUDGET / size_t(per_cu) & ~size_t(2047);  // (LDS is given out in blocks)
+  const size_t budget = lds_share(per_cu);
   const int tile = rho_tile(b, budget - head);
   // waves that share the particles (few groups) add up their sums in the tables' place
   const size_t share = rho_waves(b.min_grp, 2, BLOCK / 64) < BLOCK / 64 ? budget - head : 0;

@@ -196,8 +196,9 @@ struct LaunchBatch {
   int max_wtab;             // largest LDS shell table over systems (0: none in LDS)
   int all_wtab_lds;         // every system's shell table fits in LDS
   int all_ortho;            // every system has an orthogonal-sublattice frame (DevSys::ortho)
-  int run_threads;          // fused kernel: workgroup size (0: default for the segment count)
-  int run_waves;            // fused kernel, 256 threads: waves per SIMD it is compiled for (0: 2)
+  int run_threads;          // fused kernel: workgroup size (0: chosen by segments and walkers per CU)
+  int run_waves;            // fused kernel, 256 and 512 threads: waves per SIMD it is compiled for
+                            // (0: chosen by the walkers per CU)
   int run_chunk;            // fused kernel: moves per chunk (0: as many as LDS allows, <= RUN_CHUNK)
   int run_wpb;              // fused kernel: walkers per workgroup taken from a queue (0: one
                             // walker per workgroup, dispatched by the hardware)
@@ -216,8 +217,8 @@ struct RunPlan {
   int general_frame;  // 1 = general minimum-image reduction
   int lds_bytes;
   int blocks_per_cu;  // workgroups per CU allowed by registers
-  int waves;          // 256 threads: waves per SIMD the kernel is compiled for (512 / waves registers
-                      // per lane); 0 for the other shapes (their bound is fixed)
+  int waves;          // 256 and 512 threads: waves per SIMD the kernel is compiled for (512 / waves
+                      // registers per lane); 0 for 1024 threads (their bound is fixed)
   int walkers_per_block;  // 0: one walker per workgroup; else the queue mode's walkers per workgroup
   int grid;               // workgroups launched
 };

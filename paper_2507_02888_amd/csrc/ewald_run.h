@@ -686,7 +686,7 @@ int run_inst(const LaunchBatch& b, const RunArgs& a) {
   auto* kern = k_run<DIM, MIXED, NT, SPT, PPR, JM, PD, ORTHO, XTRA, WV, LAY, QUEUE>;
   constexpr bool DER = JM == 2 || JM == 4, UJ = JM >= 3;
   static const int per_cu = blocks_per_cu(kern, NT);
-  const size_t budget = RUN_LDS_BUDGET / size_t(per_cu);
+  const size_t budget = lds_share(per_cu);
   RunLds L{};
   int ch = b.run_chunk > 0 ? std::min(b.run_chunk, RUN_CHUNK) : RUN_CHUNK;
   size_t lds = run_layout<DIM, MIXED, NT, (JM > 0), DER, UJ>(b, ch, L);
@@ -745,6 +745,17 @@ inline int run_shape(int max_n_seg, int max_particles, int threads, int* nt, int
   return 0;
 }
 
+// Most waves per SIMD of the 256-thread kernels: the Jastrow-derivative ones
+// (JM 2, 4) spill beyond these inside the move loop.  With the u term they stay at
+// two whatever the tuning says (128 moves, ms at two, three and four waves: 250
+// electrons, 1024 walkers FP64 0.86, 1.13, 1.38, mixed 0.98, 1.57, 1.73; 2D 300
+// electrons FP64 0.67, 0.85, 1.21); without it the FP64 kernels of 3D walkers
+// with two segments per thread stop at three (250 electrons, 3000 walkers
+// 1.56, 1.37, 2.45; mixed 2.04, 1.59, 1.69).
+constexpr int run_wave_cap(int dim, bool mixed, int jm, int spt) {
+  return jm == 4 ? 2 : jm == 2 && !mixed && dim == 3 && spt == 2 ? 3 : 4;
+}
+
 // The shape when nothing is fixed, by how many walkers each CU gets: a kernel
 // bounded to w waves per SIMD holds w workgroups of 256 threads (w / 2 of 512)
 // per CU at once, each then slower than with more registers.
@@ -755,15 +766,18 @@ inline int run_shape(int max_n_seg, int max_particles, int threads, int* nt, int
 // and 0.81, FP64 0.86 and 0.70; hexagonal 2048 x 512 FP64 2.30 and 1.85, mixed 2.92
 // and 2.02; diamond 4096 x 256 mixed 4.96 and 3.68, FP64 4.08 and 3.28; bilayer
 // 2048 x 512 mixed 3.42 and 2.47.
-// The derivative kernels with the u term spill at more than two waves and stay there
-// (128 moves, ms at two, three and four: 17 electrons, 2265 walkers mixed 1.66, 2.56,
-// 3.25; 250, 1024 walkers FP64 0.92, 1.14, 1.40; without the u term mixed 0.75, 0.76, 0.66).
 // 512 < s <= 1024: two workgroups of 512 threads at four waves take 1.6 to 1.75
-// times the round of one of 1024 (N = 1024, 1024 walkers x 256 moves FP64: 1.94 and
-// 2.23 ms).  The derivative kernels run one workgroup of 512 threads with 256
+// times the round of one of 1024, with the u term up to 2 (64 moves, 1024 walkers, ms at
+// 1024 x 1 and at 512 x 2: 1024 electrons FP64 0.57 and 0.50, with u 0.79 and 0.76,
+// 800 electrons 0.53 and 0.45, with u 0.75 and 0.70, 600 electrons with u 0.63 and 0.66;
+// mixed, 512 walkers x 512 moves, 1024 electrons 3.4 and 3.0, with u 4.2 and 4.15).
+// Not so for two planes, where 512 x 2 spills around 200 registers (600 particles FP64
+// 0.50 and 0.82, mixed 0.83 and 1.06; 1000 particles 0.69 and 1.29), nor for the u
+// term in 2D FP64 (1000 electrons 0.77 and 0.89): these keep 1024 threads.
+// The derivative kernels run one workgroup of 512 threads with 256
 // registers per lane whatever the batch (with the u term and 128 moves: 1024
-// walkers 3.0 ms and 8 walkers 0.71; at 1024 threads, which spill, 3.5 and 0.84).  Walkers of more particles than the registers
-// hold, or with ions, keep 1024 threads.
+// walkers 3.0 ms and 8 walkers 0.71; at 1024 threads 3.5 and 0.84).  Walkers of more
+// particles than the registers hold, or with ions, keep 1024 threads.
 inline void run_defaults(const LaunchBatch& b, int jm, int* threads, int* waves) {
   const bool der = jm == 2 || jm == 4;
   *threads = b.run_threads;
@@ -772,19 +786,30 @@ inline void run_defaults(const LaunchBatch& b, int jm, int* threads, int* waves)
   auto rounds = [&](int per_cu) { return (b.n_walkers + per_cu * b.n_cu - 1) / (per_cu * b.n_cu); };
   int nt = 0, spt = 0, ppr = 0;
   if (!run_shape(b.max_n_seg, b.max_particles, *threads, &nt, &spt, &ppr)) return;
-  if (nt == 256 && jm != 4) {
-    const double t2 = rounds(2), t3 = rounds(3) * 1.25, t4 = rounds(4) * 1.5;
-    *waves = t2 <= t3 && t2 <= t4 ? 2 : t4 <= t3 ? 4 : 3;
+  if (nt == 256) {
+    const int cap = run_wave_cap(b.dim, b.mixed != 0, jm, spt);
+    double best = rounds(2);
+    *waves = 2;
+    for (int w = 3; w <= cap; ++w) {
+      const double t = rounds(w) * (w == 3 ? 1.25 : 1.5);
+      if (t < best || (w == 4 && *waves == 3 && t <= best)) {
+        best = t;
+        *waves = w;
+      }
+    }
   } else if (nt == 1024 && *threads == 0 && b.max_n_seg > 512 && b.max_particles > 512 && b.max_particles <= 1024 &&
-             b.max_fixed == 0 && (der || rounds(2) * 1.75 < rounds(1))) {
-    *threads = 512;
-    *waves = der ? 2 : 4;
+             b.max_fixed == 0) {
+    const bool spills = b.layered || (b.dim == 2 && !b.mixed && jm == 3);
+    if (der || (!spills && rounds(2) * 1.75 < rounds(1))) {
+      *threads = 512;
+      *waves = der ? 2 : 4;
+    }
   }
 }
 
 template <int DIM, bool MIXED, int JM, int PD, bool ORTHO, bool LAY = false>
 int run_jp(const LaunchBatch& b, const RunArgs& a) {
-  static_assert(RUN_CHUNK <= 256, "staging uses one thread per move");
+  static_assert(RUN_CHUNK <= 64, "staging and output use one lane of a wave per move");
   int nt = 0, spt = 0, ppr = 0, threads = 0, waves = 0;
   run_defaults(b, JM, &threads, &waves);
   if (!run_shape(b.max_n_seg, b.max_particles, threads, &nt, &spt, &ppr)) return RUN_NO_FIT;
@@ -793,14 +818,16 @@ int run_jp(const LaunchBatch& b, const RunArgs& a) {
   // 256-thread kernels keep them (without them the compiler spends more
   // registers there and runs slower).
   const bool xtra = b.max_particles > ppr * nt || b.max_fixed > 0;
-  const int wv = waves > 0 ? waves : 2;
+  const int wv = std::min(waves > 0 ? waves : 2, nt == 256 ? run_wave_cap(DIM, MIXED, JM, spt) : 4);
   // the queue mode is compiled for two waves per SIMD; the host rejects it
   // with other wave counts
   const bool queue = b.run_wpb > 0;
 #define EW_RUN(NT, SPT, PPR)                                                                             \
   if (nt == NT && spt == SPT && ppr == PPR) {                                                           \
-    if (wv == 3) return run_inst<DIM, MIXED, NT, SPT, PPR, JM, PD, ORTHO, true, 3, LAY>(b, a);          \
-    if (wv == 4) return run_inst<DIM, MIXED, NT, SPT, PPR, JM, PD, ORTHO, true, 4, LAY>(b, a);          \
+    if constexpr (run_wave_cap(DIM, MIXED, JM, SPT) >= 3)                                               \
+      if (wv == 3) return run_inst<DIM, MIXED, NT, SPT, PPR, JM, PD, ORTHO, true, 3, LAY>(b, a);        \
+    if constexpr (run_wave_cap(DIM, MIXED, JM, SPT) >= 4)                                               \
+      if (wv == 4) return run_inst<DIM, MIXED, NT, SPT, PPR, JM, PD, ORTHO, true, 4, LAY>(b, a);        \
     return queue ? run_inst<DIM, MIXED, NT, SPT, PPR, JM, PD, ORTHO, true, 2, LAY, true>(b, a)          \
                  : run_inst<DIM, MIXED, NT, SPT, PPR, JM, PD, ORTHO, true, 2, LAY>(b, a);               \
   }
@@ -819,10 +846,10 @@ int run_jp(const LaunchBatch& b, const RunArgs& a) {
   // registers).  The Jastrow-derivative kernels (JM 2, 4) need more registers:
   // they stay at two waves whatever the tuning says (the autotuner probes
   // without them).
-  constexpr bool DERJ = JM == 2 || JM == 4;
-  if (!DERJ && nt == 512 && spt == 2 && ppr == 2 && wv == 4 && !queue)
-    return xtra ? run_inst<DIM, MIXED, 512, 2, 2, JM, PD, ORTHO, true, 4, LAY>(b, a)
-                : run_inst<DIM, MIXED, 512, 2, 2, JM, PD, ORTHO, false, 4, LAY>(b, a);
+  if constexpr (JM != 2 && JM != 4)
+    if (nt == 512 && spt == 2 && ppr == 2 && wv == 4 && !queue)
+      return xtra ? run_inst<DIM, MIXED, 512, 2, 2, JM, PD, ORTHO, true, 4, LAY>(b, a)
+                  : run_inst<DIM, MIXED, 512, 2, 2, JM, PD, ORTHO, false, 4, LAY>(b, a);
   EW_RUN_X(512, 2, 2);
   EW_RUN_X(512, 4, 2);
 #undef EW_RUN_X
