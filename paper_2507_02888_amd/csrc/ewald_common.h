@@ -1191,6 +1191,48 @@ __device__ __forceinline__ void rho_build(const DevSys* __restrict__ S, const Po
   }
 }
 
+// rho of few particles at one segment's four slots, on the vector unit, from the
+// same phase tables (those of particles p_lo .. p_hi - 1, all of them in LDS): the
+// segment is a column piece of Q = 1, 16 FP64 operations per particle.
+// A thread per segment needs no groups and no meeting of shares, which for few
+// particles cost more than the matrix instructions save.
+template <int DIM>
+__device__ __forceinline__ void walk_sums(const DevSys* __restrict__ S, uint32_t an, const char* tabs, int p_lo,
+                                          int p_hi, cplx<double> (&v)[SEG]) {
+  static_assert(SEG == 4, "two half-integer offsets either side of the centre");
+  const int stride = S->ph_stride, ou = S->ph_ou;
+  const int n1 = DIM == 3 ? unpack_n(an, 1) : 0, c2 = 2 * unpack_n(an, DIM - 1) + SEG - 1;  // twice the centre
+  const int o0 = 16 * unpack_n(an, 0), o1 = S->ph_o1 + 16 * abs(n1), oc = ou + 16 * ((abs(c2) - 1) / 2);
+  const uint32_t s1 = n1 < 0 ? 0x80000000u : 0u, sc = c2 < 0 ? 0x80000000u : 0u;
+  double xc[2] = {}, xs[2] = {}, yc[2] = {}, ys[2] = {};  // sums of (Re, Im) A times (cos, sin)((h + 1/2) th)
+  const char* base = tabs + p_lo * stride;
+#pragma unroll 2
+  for (int p = p_lo; p < p_hi; ++p, base += stride) {
+    cplx<double> a = lds_entry(base + o0);
+    if (DIM == 3) {
+      cplx<double> e1 = lds_entry(base + o1);
+      e1.y = flip_sign(e1.y, s1);
+      a = cmul(a, e1);
+    }
+    cplx<double> ec = lds_entry(base + oc);
+    ec.y = flip_sign(ec.y, sc);
+    a = cmul(a, ec);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const cplx<double> u = lds_entry(base + ou + 16 * h);
+      xc[h] = fma(a.x, u.x, xc[h]);
+      xs[h] = fma(a.x, u.y, xs[h]);
+      yc[h] = fma(a.y, u.x, yc[h]);
+      ys[h] = fma(a.y, u.y, ys[h]);
+    }
+  }
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    v[1 - h] = {xc[h] + ys[h], yc[h] - xs[h]};
+    v[2 + h] = {xc[h] - ys[h], yc[h] + xs[h]};
+  }
+}
+
 // Waves that share the groups of column pieces in rho_build: the fewest whose
 // NS groups each cover them in one pass, so that the others share the particles.
 __host__ __device__ __forceinline__ int rho_waves(int n_grp, int ns, int nw) {

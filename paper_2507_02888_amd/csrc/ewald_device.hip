@@ -101,6 +101,55 @@ __global__ __launch_bounds__(BLOCK, UJ || (PD > 16 && ORTHO) ? 3 : 4) void k_ene
   // the tables are built from the arguments, not from spos: one trip to memory
   // before the first tile instead of three in a row
   auto frac = [&](int p, int d) { return to_frac1<DIM>(pw + p * DIM, S->Ainv, d); };
+  if (S->walk != 0 && n <= tile) {  // uniform
+    int s = tid;
+    uint32_t an;
+    double wt[SEG], at[SEG];
+    auto fetch = [&] {  // a segment's index and weights
+      an = S->seg_n[s];
+#pragma unroll
+      for (int j = 0; j < SEG; ++j) {
+        wt[j] = S->w[size_t(j) * nseg + s];
+        at[j] = S->ja ? S->ja[size_t(j) * nseg + s] : 0.0;
+      }
+    };
+    if (s < nseg) fetch();
+    fill_tables<DIM, BLOCK, false>(S, frac, S->mobile_q, 0, n, 0, tabs);
+    __syncthreads();
+    while (s < nseg) {
+      cplx<double> v[SEG];
+      walk_sums<DIM>(S, an, tabs, 0, n0, v);
+#pragma unroll
+      for (int j = 0; j < SEG; ++j) {
+        const size_t idx = size_t(j) * nseg + s;
+        if (nfix > 0) {
+          v[j].x += S->rho_fix[2 * idx];
+          v[j].y += S->rho_fix[2 * idx + 1];
+        }
+        const double m2 = v[j].x * v[j].x + v[j].y * v[j].y;
+        er = fma(wt[j], m2, er);
+        ej = fma(at[j], m2, ej);
+        rho2[idx] = {v[j].x, v[j].y};
+      }
+      if (lay) {
+        cplx<double> v1[SEG];
+        walk_sums<DIM>(S, an, tabs, n0, n, v1);
+#pragma unroll
+        for (int j = 0; j < SEG; ++j) {
+          const size_t idx = size_t(j) * nseg + s;
+          if (nfix > 0) {
+            v1[j].x += S->rho_fix1[2 * idx];
+            v1[j].y += S->rho_fix1[2 * idx + 1];
+          }
+          er = fma(wt[j], v1[j].x * v1[j].x + v1[j].y * v1[j].y, er);
+          er = fma(2.0 * S->wx[idx], v[j].x * v1[j].x + v[j].y * v1[j].y, er);
+          rho2[size_t(SEG) * nseg + idx] = {v1[j].x, v1[j].y};
+        }
+      }
+      s += BLOCK;
+      if (s < nseg) fetch();
+    }
+  } else {
   rho_build<DIM, BLOCK / 64, 2, true, false>(S, frac, S->mobile_q, n0, tabs, tile, rc, rc_bytes, gw, 0, S->n_grp,
                                 [&](int idx, cplx<double> v, double2 w2) {
                                   if (nfix > 0) {
@@ -127,6 +176,7 @@ __global__ __launch_bounds__(BLOCK, UJ || (PD > 16 && ORTHO) ? 3 : 4) void k_ene
                                     er = fma(2.0 * S->wx[idx], v0.x * v.x + v0.y * v.y, er);
                                     rho12[idx] = {v.x, v.y};
                                   });
+  }
   }
   __syncthreads();  // the tables (and rc) are done with
 
@@ -642,13 +692,15 @@ __global__ __launch_bounds__(BLOCK) void k_accept(const DevSys* __restrict__ sys
 // nothing to do.
 // Large batches take `per` walkers per workgroup in turn, as the launch of
 // workgroups that find nothing due costs more than two due walkers now and then
-// meeting in one (32,768 workgroups of 8 waves take 24 us).
+// meeting in one (32,768 workgroups of 8 waves take 24 us).  Walkers of up to 40
+// particles (rho by segments, little work each) take four waves and fewer walkers per workgroup
+// (16 steps of 6000 walkers of 8 electrons, 2D: 1102 us with eight waves and 11 walkers, 960 with
+// two walkers, 870 so; 54 electrons in 3D, 64 walkers: 318 with eight waves, 329 with four).
 // The counter is reset by the next accept or run call, not here, so that
 // every chunk sees the same trigger.
-constexpr int REBUILD_NT = 512;
 constexpr int REBUILD_GROUPS = 4;
-template <int DIM>
-__global__ __launch_bounds__(REBUILD_NT) void k_rebuild(const DevSys* __restrict__ systems,
+template <int DIM, int NT>
+__global__ __launch_bounds__(NT) void k_rebuild(const DevSys* __restrict__ systems,
                                                         const DevWalker* __restrict__ walkers,
                                                         char* __restrict__ state, int tile, int rc_bytes, int n_walkers,
                                                         int per) {
@@ -661,7 +713,7 @@ __global__ __launch_bounds__(REBUILD_NT) void k_rebuild(const DevSys* __restrict
     const DevWalker Wi = walkers[w0 + (threadIdx.x & 63)];
     const DevSys* Si = systems + Wi.sys;
     due_i = Si->refresh_every > 0 && reinterpret_cast<const WalkerHdr*>(state + Wi.state_off)->counter >= Si->refresh_every &&
-            g_lo < Si->n_grp;
+            g_lo < (Si->walk != 0 && Wi.n_mobile <= tile ? 1 : Si->n_grp);
   }
   for (uint64_t due = __ballot(due_i); due != 0; due &= due - 1) {  // uniform
   const DevWalker W = walkers[w0 + __builtin_ctzll(due)];
@@ -672,7 +724,7 @@ __global__ __launch_bounds__(REBUILD_NT) void k_rebuild(const DevSys* __restrict
   const double* spos = reinterpret_cast<const double*>(st + HDR_BYTES);
   double* rho = reinterpret_cast<double*>(st + HDR_BYTES + walker_pos_bytes(n, DIM));
   const int g_hi = min(g_lo + REBUILD_GROUPS, S->n_grp);
-  const int gw = rho_waves(g_hi - g_lo, 1, REBUILD_NT / 64);
+  const int gw = rho_waves(g_hi - g_lo, 1, NT / 64);
   char* tabs = reinterpret_cast<char*>(smem);
   double drift = 0.0;
   // a layered system: each plane from its own particles and ions
@@ -681,8 +733,30 @@ __global__ __launch_bounds__(REBUILD_NT) void k_rebuild(const DevSys* __restrict
     const int p0 = l == 0 ? 0 : S->n0, p1 = n_planes == 1 ? n : (l == 0 ? S->n0 : n);
     double2* rl = reinterpret_cast<double2*>(rho) + size_t(SEG) * nseg * l;
     const double* rfix = S->n_fixed > 0 ? (l == 0 ? S->rho_fix : S->rho_fix1) : nullptr;
+    if (S->walk != 0 && n <= tile) {  // uniform; the first chunk takes all segments
+      fill_tables<DIM, NT, false>(S, [&](int p, int d) { return spos[(p0 + p) * DIM + d]; }, S->mobile_q + p0, 0,
+                                          p1 - p0, 0, tabs);
+      __syncthreads();
+      for (int s = threadIdx.x; s < nseg; s += NT) {
+        cplx<double> v[SEG];
+        walk_sums<DIM>(S, S->seg_n[s], tabs, 0, p1 - p0, v);
+#pragma unroll
+        for (int j = 0; j < SEG; ++j) {
+          const size_t idx = size_t(j) * nseg + s;
+          if (rfix) {
+            v[j].x += rfix[2 * idx];
+            v[j].y += rfix[2 * idx + 1];
+          }
+          const double2 old = rl[idx];
+          drift = fmax(drift, fmax(fabs(v[j].x - old.x), fabs(v[j].y - old.y)));
+          rl[idx] = {v[j].x, v[j].y};
+        }
+      }
+      __syncthreads();
+      continue;
+    }
     // the waves' shares meet in the tables' LDS (one pass, after their last use)
-    rho_build<DIM, REBUILD_NT / 64, 1, false, false>(S, [&](int p, int d) { return spos[(p0 + p) * DIM + d]; },
+    rho_build<DIM, NT / 64, 1, false, false>(S, [&](int p, int d) { return spos[(p0 + p) * DIM + d]; },
                                        S->mobile_q + p0, p1 - p0, tabs, tile, reinterpret_cast<cplx<double>*>(smem), rc_bytes, gw, g_lo, g_hi,
                                        [&](int idx, cplx<double> v, double2) {
                                          if (rfix) {
@@ -784,17 +858,23 @@ int delta_dim(const LaunchBatch& b, char* state, const int32_t* k, const double*
   return last_launch();
 }
 
-template <int DIM>
-int rebuild_launch(const LaunchBatch& b, char* state, void* stream) {
+template <int DIM, int NT>
+int rebuild_inst(const LaunchBatch& b, char* state, void* stream) {
   const int tile = rho_tile(b, RUN_LDS_BUDGET / 2);
   const int chunks = (b.max_grp + REBUILD_GROUPS - 1) / REBUILD_GROUPS;
   const size_t lds = std::max(rho_lds(b, tile), size_t(REBUILD_GROUPS) * GRP_BYTES);
-  auto* kern = k_rebuild<DIM>;
+  auto* kern = k_rebuild<DIM, NT>;
   if (int rc = allow_lds(kern, lds)) return rc;
-  const int per = std::max(1, std::min(16, b.n_walkers / 512));
-  hipLaunchKernelGGL(kern, dim3((b.n_walkers + per - 1) / per, chunks), dim3(REBUILD_NT), lds, as_stream(stream),
+  // about 2048 workgroups of eight waves, or twice as many of four
+  const int per = int(std::max(1ll, std::min(16ll, (long long)b.n_walkers * chunks * NT / (512 * 2048))));
+  hipLaunchKernelGGL(kern, dim3((b.n_walkers + per - 1) / per, chunks), dim3(NT), lds, as_stream(stream),
                      b.d_sys, b.d_walk, state, tile, int(lds), b.n_walkers, per);
   return last_launch();
+}
+
+template <int DIM>
+int rebuild_launch(const LaunchBatch& b, char* state, void* stream) {
+  return b.max_particles <= 40 ? rebuild_inst<DIM, 256>(b, state, stream) : rebuild_inst<DIM, 512>(b, state, stream);
 }
 
 template <int DIM, bool MIXED>

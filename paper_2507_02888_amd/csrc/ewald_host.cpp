@@ -828,6 +828,16 @@ ewald_status ewald_setup(const ewald_sys_desc* desc, ewald_sys** out) try {
         }
     }
     DevSys& D = S->dev;
+    // Few particles: rho by segments on the vector unit (walk_sums).  The groups
+    // cost a fixed time, the most where pieces fill them badly, as in 2D.  Energy
+    // calls, 1500 walkers, us by groups and by segments: 90 segments, 8 particles 18.4 and
+    // 16.4, 40 particles 26.3 and 25.8, 80 particles 37.6 and 39.7; 2D 28 segments, 40
+    // particles 20.5 and 19.0, 64 particles 25.1 and 24.4; two planes of 108 segments, 8
+    // particles 51 and 18, 64 particles 62 and 33; 210 segments, 64 particles 44 and 42;
+    // 803 segments, 40 particles 65 and 64, 64 particles 85 and 94.
+    D.walk = S->n_mobile <= 40 || (S->n_mobile <= 64 && n_seg > 96 && n_seg <= 256) ? 1 : 0;
+    if (D.walk)  // the tables reach every segment's centre
+      for (const Seg& sg : segs) hn = std::max(hn, (std::abs(2 * sg.n[last] + SEG - 1) - 1) / 2 + 1);
     D.n_grp = n_grp;
     D.n_ent = off;
     // A particle's partners in as many shares as make the workgroup's rounds (an

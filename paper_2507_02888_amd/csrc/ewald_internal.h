@@ -135,6 +135,7 @@ struct DevSys {
   // partners per share of the loop over all particles alike and of the rest
   int pair_parts, pair_full, pair_more;
   int ph_hn, ph_o1, ph_ou, ph_stride, ph_runs;
+  int walk;  // few particles: rho by segments from the same tables (walk_sums), not by groups
   const int32_t* grp_q;
   const int32_t* grp_off;
   const uint32_t* grp_col;
