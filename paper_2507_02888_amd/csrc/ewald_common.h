@@ -956,7 +956,8 @@ struct SegWalk {
 // run together their times add.)
 // Bound by FP64 issue.  At N = 1024 (254 columns, 3960 entries) 1024 rebuilds by
 // the per-step calls take 0.84 ms with their accepts (1.66 ms by walking the
-// columns, eight operations per entry), 1024 energies 1.65 ms (2.2 ms).
+// columns, eight operations per entry), 1024 energies 1.55 ms (2.1 ms).  Few
+// particles go by segments instead (walk_sums below).
 //
 // Lanes (operand A: piece l % 16, particle l / 16; operand B: column l % 4,
 // particle l / 16; result: column l % 4, piece 4 (l / 4 % 4) + l / 16).
@@ -971,9 +972,9 @@ struct SegWalk {
 // longest pieces at the least; the tables' own may serve, such a pass being the only
 // one), in a fixed order: where every share's sums fit, all waves then take a
 // part of the entries, else one share after the other adds its own.  (Small systems
-// wait for this end, not for arithmetic: a bilayer of 40 electrons, 30 walkers, takes
-// 17.5 us per energy call so, 29.0 one share after the other, its loads in
-// between.)
+// wait for this end, not for arithmetic: by groups, a bilayer of 40 electrons, 30 walkers,
+// took 17.5 us per energy call so, 29.0 one share after the other, its loads in
+// between; by segments 10.)
 // Each pass takes the particles `tile` at a time (a multiple of four) through LDS
 // phase tables at `tabs` (S->ph_stride bytes per particle), from the fractional
 // coordinates frac(p, d).  `sink(idx, v, w)`

@@ -14,11 +14,11 @@
 // j * n_seg + s) so that one wave instruction reads 64 consecutive entries.
 //
 // One workgroup serves one walker in every kernel (256 threads in the energy
-// and per-step kernels); reductions are wave shuffles followed by an LDS
-// combine.  rho from the positions is a contraction over the particles and
-// runs on the FP64 matrix instructions (rho_build); a move's phases are
-// complex multiplies with depth 1 and the pair work is a reciprocal square
-// root and a polynomial, neither of which is one.
+// and per-step kernels); reductions go through rows of 16 lanes, then LDS.
+// rho from the positions is a contraction over the particles and runs on the
+// FP64 matrix instructions (rho_build; few particles by segments, walk_sums);
+// a move's phases are complex multiplies with depth 1 and the pair work is a
+// reciprocal square root and a polynomial, neither of which is one.
 //
 // This translation unit holds the energy, per-step delta/accept and rebuild
 // kernels, the fused kernel's dispatch, and the device memory helpers; the
@@ -36,8 +36,8 @@ namespace ewald {
 // of one sign (like charges), so any FP32 rounding bias of the pair function
 // would add up coherently, while in a move delta it cancels between the old
 // and new terms.  The pair loop works in the orthogonal-sublattice frame when
-// the cell has one (ORTHO); rho is built from the fractional positions just
-// stored in the walker state.
+// the cell has one (ORTHO); rho is built from the positions given, wrapped as they
+// are for the walker state.
 // UJ: the Jastrow value also takes the two-body polynomial term u over the
 // mobile pairs (Sec. 2.3, Eq. (8)).
 // Registers: four waves per SIMD (128 per lane) hold the loops without the u term;
