@@ -428,9 +428,10 @@ def layers_row(forms=("mixed", "fp64"), steps: int = 2):
 def blip_row(reps: int = 5):
     """Batched blip orbitals: 512 orbitals on a 40^3 grid over the N=1024
     cell at 65536 proposal points per call, values, gradients and
-    Laplacians; points/s and the kernel's fraction of HBM bandwidth by the
-    algorithmic bytes (64 coefficient rows read, 5 outputs written per
-    orbital and point)."""
+    Laplacians; points/s, the call's fraction of HBM bandwidth by the bytes
+    that it cannot do without (the coefficients once, 5 outputs per orbital and
+    point), and the rate of the rows that the points gather through the caches
+    (64 per point)."""
     import torch
     from paper_2507_02888_amd import ewald as ew
     from paper_2507_02888_amd import workloads as wl
@@ -454,14 +455,16 @@ def blip_row(reps: int = 5):
     e1.record(stream)
     torch.cuda.synchronize()
     ms = e0.elapsed_time(e1) / reps
-    bytes_per_point = BLIP_WINDOW * M * 8 + 5 * M * 8 + 24
+    bytes_per_point = coef.numel() * 8 / P + 5 * M * 8 + 24
     gbs = P * bytes_per_point / (ms * 1e-3) / 1e9
+    rows_gbs = P * BLIP_WINDOW * M * 8 / (ms * 1e-3) / 1e9
     coef_mb = coef.numel() * 8 / 1e6
     b.close()
     return dict(points_per_s=round(P / (ms * 1e-3), 1), launch_ms=round(ms, 4), points=P, orbitals=M,
                 grid=list(wl.BLIP_GRID), coefficient_mb=round(coef_mb, 1),
                 roofline=dict(bound="hbm", achieved=round(gbs, 1), peak=PEAK_HBM_GBS, unit="GB/s",
-                              frac=round(gbs / PEAK_HBM_GBS, 4), bytes_per_point=bytes_per_point),
+                              frac=round(gbs / PEAK_HBM_GBS, 4), bytes_per_point=round(bytes_per_point, 1),
+                              rows_gbs=round(rows_gbs, 1)),
                 call="ewald_blip_eval_batch (values, gradients, Laplacians; FP64)")
 
 
