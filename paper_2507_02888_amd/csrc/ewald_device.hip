@@ -45,8 +45,11 @@ namespace ewald {
 // them were spilled inside the pair loop, and three waves (168) are faster at
 // any batch (ms, N = 1024, 1024 walkers, with u: 2.6 and 2.35; degree 32: 2.67 and 1.52;
 // 256 walkers with u 1.19 and 0.87).
+// WALK: rho by segments (walk_sums), in a kernel of its own, for batches all of whose
+// walkers have few particles; both ways in one kernel cost the large walkers 1 % of
+// their energies (N = 1024 with the u term 2334 and 2363 us).
 constexpr int RED_ENERGY = 48;  // LDS doubles for k_energy's reduction
-template <int DIM, int PD, bool ORTHO, bool UJ>
+template <int DIM, int PD, bool ORTHO, bool UJ, bool WALK>
 __global__ __launch_bounds__(BLOCK, UJ || (PD > 16 && ORTHO) ? 3 : 4) void k_energy(const DevSys* __restrict__ systems,
                                                   const DevWalker* __restrict__ walkers,
                                                   const double* __restrict__ pos, char* __restrict__ state,
@@ -94,14 +97,12 @@ __global__ __launch_bounds__(BLOCK, UJ || (PD > 16 && ORTHO) ? 3 : 4) void k_ene
   // follows the first in the state
   const bool lay = DIM == 2 && S->n_layers > 1;
   const int n0 = lay ? S->n0 : n;
-  const int gw = rho_waves(S->n_grp, 2, BLOCK / 64);
-  cplx<double>* rc = reinterpret_cast<cplx<double>*>(tabs);  // waves sharing the particles: one pass, after the tables' last use
   double2* rho2 = reinterpret_cast<double2*>(rho);
   double er = 0.0, ej = 0.0;
   // the tables are built from the arguments, not from spos: one trip to memory
   // before the first tile instead of three in a row
   auto frac = [&](int p, int d) { return to_frac1<DIM>(pw + p * DIM, S->Ainv, d); };
-  if (S->walk != 0 && n <= tile) {  // uniform
+  if constexpr (WALK) {
     int s = tid;
     uint32_t an;
     double wt[SEG], at[SEG];
@@ -150,6 +151,8 @@ __global__ __launch_bounds__(BLOCK, UJ || (PD > 16 && ORTHO) ? 3 : 4) void k_ene
       if (s < nseg) fetch();
     }
   } else {
+  const int gw = rho_waves(S->n_grp, 2, BLOCK / 64);
+  cplx<double>* rc = reinterpret_cast<cplx<double>*>(tabs);  // waves sharing the particles: one pass, after the tables' last use
   rho_build<DIM, BLOCK / 64, 2, true, false>(S, frac, S->mobile_q, n0, tabs, tile, rc, rc_bytes, gw, 0, S->n_grp,
                                 [&](int idx, cplx<double> v, double2 w2) {
                                   if (nfix > 0) {
@@ -692,14 +695,14 @@ __global__ __launch_bounds__(BLOCK) void k_accept(const DevSys* __restrict__ sys
 // nothing to do.
 // Large batches take `per` walkers per workgroup in turn, as the launch of
 // workgroups that find nothing due costs more than two due walkers now and then
-// meeting in one (32,768 workgroups of 8 waves take 24 us).  Walkers of up to 40
-// particles (rho by segments, little work each) take four waves and fewer walkers per workgroup
-// (16 steps of 6000 walkers of 8 electrons, 2D: 1102 us with eight waves and 11 walkers, 960 with
-// two walkers, 870 so; 54 electrons in 3D, 64 walkers: 318 with eight waves, 329 with four).
+// meeting in one (32,768 workgroups of 8 waves take 24 us).
+// WALK: rho by segments, one chunk of four waves, for batches all of whose walkers have
+// few particles; with so little work a workgroup takes fewer walkers (16 steps of 6000
+// walkers of 8 electrons, 2D: 1102 us by groups with eight waves and 11 walkers, 870 so).
 // The counter is reset by the next accept or run call, not here, so that
 // every chunk sees the same trigger.
 constexpr int REBUILD_GROUPS = 4;
-template <int DIM, int NT>
+template <int DIM, int NT, bool WALK>
 __global__ __launch_bounds__(NT) void k_rebuild(const DevSys* __restrict__ systems,
                                                         const DevWalker* __restrict__ walkers,
                                                         char* __restrict__ state, int tile, int rc_bytes, int n_walkers,
@@ -713,7 +716,7 @@ __global__ __launch_bounds__(NT) void k_rebuild(const DevSys* __restrict__ syste
     const DevWalker Wi = walkers[w0 + (threadIdx.x & 63)];
     const DevSys* Si = systems + Wi.sys;
     due_i = Si->refresh_every > 0 && reinterpret_cast<const WalkerHdr*>(state + Wi.state_off)->counter >= Si->refresh_every &&
-            g_lo < (Si->walk != 0 && Wi.n_mobile <= tile ? 1 : Si->n_grp);
+            (WALK || g_lo < Si->n_grp);
   }
   for (uint64_t due = __ballot(due_i); due != 0; due &= due - 1) {  // uniform
   const DevWalker W = walkers[w0 + __builtin_ctzll(due)];
@@ -723,8 +726,6 @@ __global__ __launch_bounds__(NT) void k_rebuild(const DevSys* __restrict__ syste
   WalkerHdr* hdr = reinterpret_cast<WalkerHdr*>(st);
   const double* spos = reinterpret_cast<const double*>(st + HDR_BYTES);
   double* rho = reinterpret_cast<double*>(st + HDR_BYTES + walker_pos_bytes(n, DIM));
-  const int g_hi = min(g_lo + REBUILD_GROUPS, S->n_grp);
-  const int gw = rho_waves(g_hi - g_lo, 1, NT / 64);
   char* tabs = reinterpret_cast<char*>(smem);
   double drift = 0.0;
   // a layered system: each plane from its own particles and ions
@@ -733,7 +734,7 @@ __global__ __launch_bounds__(NT) void k_rebuild(const DevSys* __restrict__ syste
     const int p0 = l == 0 ? 0 : S->n0, p1 = n_planes == 1 ? n : (l == 0 ? S->n0 : n);
     double2* rl = reinterpret_cast<double2*>(rho) + size_t(SEG) * nseg * l;
     const double* rfix = S->n_fixed > 0 ? (l == 0 ? S->rho_fix : S->rho_fix1) : nullptr;
-    if (S->walk != 0 && n <= tile) {  // uniform; the first chunk takes all segments
+    if constexpr (WALK) {
       fill_tables<DIM, NT, false>(S, [&](int p, int d) { return spos[(p0 + p) * DIM + d]; }, S->mobile_q + p0, 0,
                                           p1 - p0, 0, tabs);
       __syncthreads();
@@ -752,9 +753,9 @@ __global__ __launch_bounds__(NT) void k_rebuild(const DevSys* __restrict__ syste
           rl[idx] = {v[j].x, v[j].y};
         }
       }
-      __syncthreads();
-      continue;
-    }
+    } else {
+    const int g_hi = min(g_lo + REBUILD_GROUPS, S->n_grp);
+    const int gw = rho_waves(g_hi - g_lo, 1, NT / 64);
     // the waves' shares meet in the tables' LDS (one pass, after their last use)
     rho_build<DIM, NT / 64, 1, false, false>(S, [&](int p, int d) { return spos[(p0 + p) * DIM + d]; },
                                        S->mobile_q + p0, p1 - p0, tabs, tile, reinterpret_cast<cplx<double>*>(smem), rc_bytes, gw, g_lo, g_hi,
@@ -767,6 +768,7 @@ __global__ __launch_bounds__(NT) void k_rebuild(const DevSys* __restrict__ syste
                                          drift = fmax(drift, fmax(fabs(v.x - old.x), fabs(v.y - old.y)));
                                          rl[idx] = {v.x, v.y};
                                        });
+    }
     __syncthreads();
   }
   for (int off = 32; off > 0; off >>= 1) drift = fmax(drift, __shfl_xor(drift, off, 64));
@@ -782,20 +784,22 @@ __global__ __launch_bounds__(NT) void k_rebuild(const DevSys* __restrict__ syste
 
 namespace {
 
-template <int DIM, int PD, bool ORTHO, bool UJ>
+template <int DIM, int PD, bool ORTHO, bool UJ, bool WALK>
 int energy_inst(const LaunchBatch& b, const double* pos, char* state, double* energy, double* jastrow,
                 void* stream) {
   const int lds_pos = even(b.max_particles);
   const size_t head = RED_ENERGY * 8, pairs = size_t(lds_pos) * (DIM + 1) * 8;
-  auto* kern = k_energy<DIM, PD, ORTHO, UJ>;
+  auto* kern = k_energy<DIM, PD, ORTHO, UJ, WALK>;
   // phase-table tiles (sharing their LDS with the pair loop's positions) as
   // large as LDS allows without lowering the workgroups per CU that
   // registers allow (three or four)
   static const int per_cu = blocks_per_cu(kern, BLOCK);
   const size_t budget = lds_share(per_cu);
   const int tile = rho_tile(b, budget - head);
+  if constexpr (WALK)  // one tile holds every particle, or the groups take turns at smaller ones
+    if (tile < b.max_particles) return energy_inst<DIM, PD, ORTHO, UJ, false>(b, pos, state, energy, jastrow, stream);
   // waves that share the particles (few groups) add up their sums in the tables' place
-  const size_t share = rho_waves(b.min_grp, 2, BLOCK / 64) < BLOCK / 64 ? budget - head : 0;
+  const size_t share = !WALK && rho_waves(b.min_grp, 2, BLOCK / 64) < BLOCK / 64 ? budget - head : 0;
   static_assert(size_t(BLOCK / 64) * GRP_BYTES + RED_ENERGY * 8 <= RUN_LDS_BUDGET / 4, "shares' sums too large");
   const size_t lds = head + std::max({pairs, rho_lds(b, tile), share});
   if (int rc = allow_lds(kern, lds)) return rc;
@@ -807,8 +811,11 @@ int energy_inst(const LaunchBatch& b, const double* pos, char* state, double* en
 template <int DIM, int PD, bool ORTHO>
 int energy_pd(const LaunchBatch& b, const double* pos, char* state, double* energy, double* jastrow,
               void* stream) {
-  return b.has_u ? energy_inst<DIM, PD, ORTHO, true>(b, pos, state, energy, jastrow, stream)
-                 : energy_inst<DIM, PD, ORTHO, false>(b, pos, state, energy, jastrow, stream);
+  if (b.all_walk)
+    return b.has_u ? energy_inst<DIM, PD, ORTHO, true, true>(b, pos, state, energy, jastrow, stream)
+                   : energy_inst<DIM, PD, ORTHO, false, true>(b, pos, state, energy, jastrow, stream);
+  return b.has_u ? energy_inst<DIM, PD, ORTHO, true, false>(b, pos, state, energy, jastrow, stream)
+                 : energy_inst<DIM, PD, ORTHO, false, false>(b, pos, state, energy, jastrow, stream);
 }
 
 template <int DIM>
@@ -858,12 +865,14 @@ int delta_dim(const LaunchBatch& b, char* state, const int32_t* k, const double*
   return last_launch();
 }
 
-template <int DIM, int NT>
+template <int DIM, int NT, bool WALK>
 int rebuild_inst(const LaunchBatch& b, char* state, void* stream) {
   const int tile = rho_tile(b, RUN_LDS_BUDGET / 2);
-  const int chunks = (b.max_grp + REBUILD_GROUPS - 1) / REBUILD_GROUPS;
-  const size_t lds = std::max(rho_lds(b, tile), size_t(REBUILD_GROUPS) * GRP_BYTES);
-  auto* kern = k_rebuild<DIM, NT>;
+  if constexpr (WALK)
+    if (tile < b.max_particles) return rebuild_inst<DIM, 512, false>(b, state, stream);
+  const int chunks = WALK ? 1 : (b.max_grp + REBUILD_GROUPS - 1) / REBUILD_GROUPS;
+  const size_t lds = std::max(rho_lds(b, tile), WALK ? size_t(0) : size_t(REBUILD_GROUPS) * GRP_BYTES);
+  auto* kern = k_rebuild<DIM, NT, WALK>;
   if (int rc = allow_lds(kern, lds)) return rc;
   // about 2048 workgroups of eight waves, or twice as many of four
   const int per = int(std::max(1ll, std::min(16ll, (long long)b.n_walkers * chunks * NT / (512 * 2048))));
@@ -874,7 +883,7 @@ int rebuild_inst(const LaunchBatch& b, char* state, void* stream) {
 
 template <int DIM>
 int rebuild_launch(const LaunchBatch& b, char* state, void* stream) {
-  return b.max_particles <= 40 ? rebuild_inst<DIM, 256>(b, state, stream) : rebuild_inst<DIM, 512>(b, state, stream);
+  return b.all_walk ? rebuild_inst<DIM, 256, true>(b, state, stream) : rebuild_inst<DIM, 512, false>(b, state, stream);
 }
 
 template <int DIM, bool MIXED>

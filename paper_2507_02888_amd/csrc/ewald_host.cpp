@@ -1328,6 +1328,7 @@ ewald_status ewald_batch_create(ewald_sys* const* sys, int n_sys, const int* wal
   if (dev_cu_count(&L.n_cu) != 0 || L.n_cu < 1) L.n_cu = 1;
   L.all_wtab_lds = 1;
   L.all_ortho = 1;
+  L.all_walk = 1;
   L.n_walkers = n_walkers;
   L.dim = dim;
   L.mixed = sys[0]->precision == EWALD_FP32_MIXED ? 1 : 0;
@@ -1348,6 +1349,7 @@ ewald_status ewald_batch_create(ewald_sys* const* sys, int n_sys, const int* wal
     L.max_wtab = std::max(L.max_wtab, sys[i]->dev_uploaded.wtab_lds ? sys[i]->dev_uploaded.n_wtab : 0);
     L.all_wtab_lds &= sys[i]->dev_uploaded.wtab_lds;
     L.all_ortho &= sys[i]->dev.ortho;
+    L.all_walk &= sys[i]->dev.walk;
   }
   rc = dev_alloc(&B->d_sys, ds.size() * sizeof(DevSys));
   if (rc) return fail(EWALD_E_NOMEM, "device allocation failed");

@@ -205,6 +205,7 @@ struct LaunchBatch {
                             // walker per workgroup, dispatched by the hardware)
   int n_cu;                 // compute units of the device
   int general_frame;        // fused kernel: 1 = general minimum-image reduction even if all_ortho
+  int all_walk;             // every system builds rho by segments (DevSys::walk)
 };
 
 // The fused kernel's launch shape for a batch (all zero: it does not fit and
