@@ -213,7 +213,10 @@ void ewald_batch_destroy(ewald_batch *b);
  *   state    device, ewald_batch_layout bytes; (re)initialised: wrapped
  *            positions, rho in FP64, counters zeroed, no pending move
  *   energy   device [n_walkers] out
- *   jastrow  device [n_walkers] out, or NULL */
+ *   jastrow  device [n_walkers] out, or NULL
+ * Systems of few particles (up to 40, or up to 64) are summed in another order
+ * where every system of the batch is so: the rounding of their walkers may depend on
+ * whether the batch holds larger ones too. */
 ewald_status ewald_energy_batch(ewald_batch *b, const double *pos, void *state, double *energy,
                                 double *jastrow, void *stream);
 

@@ -116,3 +116,34 @@ def test_step_rebuilds_of_many_walkers(W, n, gmul, planes):
         for p in range(planes):
             ref, tol = direct(h, s, b.walker_positions(int(w)), p)
             assert np.max(np.abs(b.walker_rho(int(w), p) - ref)) <= tol, (w, p)
+
+
+@pytest.mark.parametrize("sizes", [((12, 5.0), (40, 9.0)), ((12, 5.0), (90, 9.0)), ((3, 11.0), (64, 7.0), (33, 4.0)),
+                                   ((3, 11.0), (65, 7.0), (300, 4.0))])
+def test_systems_in_one_batch(oracle_lib, sizes):
+    """Systems of several sizes and cutoffs together: all of few particles, and beside larger ones."""
+    K, S, reps = 2, 4, 3
+    ss = [system(3, n, g, 1, i) for i, (n, g) in enumerate(sizes)]
+    hs = [ew.System(s, precision=ew.EWALD_FP32_MIXED, refresh_every=K) for s in ss]
+    which = np.tile(np.arange(len(ss), dtype=np.int32), reps)
+    W, f = len(which), dict(device="cuda")
+    b = ew.Batch(hs, which)
+    rng = np.random.default_rng([64, len(ss), ss[1].n_mobile])
+    pos = [rng.uniform(-7, 14, (ss[i].n_mobile, 3)) for i in which]
+    e, d = torch.zeros(W, dtype=torch.float64, **f), torch.zeros(W, dtype=torch.float64, **f)
+    b.energy(torch.tensor(np.concatenate(pos), **f), e)
+    torch.cuda.synchronize()
+    for w, i in enumerate(which):
+        ref, tol = direct(hs[i], ss[i], b.walker_positions(w), 0)
+        assert np.max(np.abs(b.walker_rho(w) - ref)) <= tol, w
+        ref = oracle_lib.energy(ss[i], *oracle_lib.particles(ss[i], pos[w]))["total"]
+        scale = max(abs(ref), ss[i].alpha / math.sqrt(math.pi) * float((ss[i].mobile_q ** 2).sum() + (ss[i].fixed_q ** 2).sum()))
+        assert abs(float(e[w]) - ref) <= 1e-10 * scale
+    for m in range(S):  # every walker due after the second and the fourth
+        k = np.array([rng.integers(ss[i].n_mobile) for i in which], np.int32)
+        b.move_delta(torch.tensor(k, **f), torch.tensor(rng.uniform(-7, 14, (W, 3)), **f), d)
+        b.accept(torch.ones(W, dtype=torch.uint8, **f))
+    torch.cuda.synchronize()
+    for w, i in enumerate(which):
+        ref, tol = direct(hs[i], ss[i], b.walker_positions(w), 0)
+        assert np.max(np.abs(b.walker_rho(w) - ref)) <= tol, w
